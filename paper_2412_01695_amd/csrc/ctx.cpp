@@ -181,10 +181,11 @@ void clear_q(pw_ctx* c) {
 void free_kdata(pw_ctx* c) {
   for (void** p : {(void**)&c->d_npw, (void**)&c->d_nstick, (void**)&c->d_gmap, (void**)&c->d_sof,
                    (void**)&c->d_kin, (void**)&c->d_mkey, (void**)&c->d_lexperm, (void**)&c->d_beta64,
-                   (void**)&c->d_beta32}) {
+                   (void**)&c->d_beta32, &c->d_vk64, &c->d_vk32}) {
     dev_free(c, *p);
     *p = nullptr;
   }
+  c->kmesh = 0;
   c->have_k = false;
   c->have_proj = false;
   c->nproj = 0;
@@ -198,8 +199,8 @@ void free_all(pw_ctx* c) {
     dev_free(c, *p);
     *p = nullptr;
   }
-  c->vperm_l3c64 = c->vperm_l3c32 = 0;
-  c->xtaps_wc64 = c->xtaps_wc32 = 0;
+  c->vperm_key64 = c->vperm_key32 = 0;
+  c->xtaps_key64 = c->xtaps_key32 = 0;
   c->have_v = false;
 }
 
@@ -621,6 +622,7 @@ pw_status pw_set_kpoints(pw_ctx* c, int nk, const double* k, int32_t* npw_out, i
     HIPCHK(c, hipStreamSynchronize(c->stream));
   }
   c->have_k = true;
+  hpsi_potential_build(c);
   return PW_OK;
 }
 
@@ -665,14 +667,15 @@ pw_status pw_set_vloc(pw_ctx* c, const double* v) {
   dev_free(c, c->d_v32);
   c->d_v64 = nullptr;
   c->d_v32 = nullptr;
-  c->vperm_l3c64 = c->vperm_l3c32 = 0;  // permuted copies and x taps are rebuilt from the new potential
-  c->xtaps_wc64 = c->xtaps_wc32 = 0;
+  c->vperm_key64 = c->vperm_key32 = 0;  // permuted copies and x taps are rebuilt from the new potential
+  c->xtaps_key64 = c->xtaps_key32 = 0;
   c->have_v = false;
   pw_status s;
   if ((s = upload(c, v64.data(), nr, &c->d_v64)) != PW_OK) return s;
   if ((s = upload(c, v32.data(), nr, &c->d_v32)) != PW_OK) return s;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->have_v = true;
+  hpsi_potential_build(c);
   return PW_OK;
 }
 

@@ -30,7 +30,9 @@ constexpr int kMeshes[] = {15, 18, 20, 24, 30, 32, 36};
 
 template <class T>
 pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st, void* vscratch) {
-  switch (c->fft[0]) {
+  // an explicit launch shape is one of the context's own mesh
+  const bool own_mesh = c->kmesh == 0 || c->hpsi_variant != 0 || c->hpsi_slab != 0 || c->hpsi_threads != 0;
+  switch (own_mesh ? c->fft[0] : c->kmesh) {
     case 15: return launch_n<T, 15>(c, sel, psi, hpsi, st, vscratch);
     case 18: return launch_n<T, 18>(c, sel, psi, hpsi, st, vscratch);
     case 20: return launch_n<T, 20>(c, sel, psi, hpsi, st, vscratch);
@@ -83,6 +85,12 @@ bool hpsi_supported(int n1, int n2, int n3) {
   for (int n : kMeshes)
     if (n == n1) return true;
   return false;
+}
+
+int hpsi_mesh_at_least(int n) {
+  for (int m : kMeshes)
+    if (m >= n) return m;
+  return 0;
 }
 
 pw_status launch_hpsi(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st,

@@ -697,43 +697,49 @@ pw_status launch_shape(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi
   if (ntask <= 0) return PW_OK;
   if (ntask > (1L << 30)) return set_err(c, PW_EINVAL, "too many (k, band) rows in one call");
   const bool fp64 = sizeof(T) == 8;
-  const T* v = (const T*)(fp64 ? (const void*)c->d_v64 : (const void*)c->d_v32);
+  // V/N_r on this mesh: the context's, or the smaller one of the autotuned
+  // launches
+  const bool own_mesh = N == c->fft[0];
+  const double* v64 = own_mesh ? c->d_v64 : (const double*)c->d_vk64;
+  const T* v = fp64 ? (const T*)(const void*)v64 : (const T*)(own_mesh ? (const void*)c->d_v32 : c->d_vk32);
   void* vp = vscratch;
   const size_t taps_bytes = (size_t)N * N * (2 * WC - 1) * sizeof(cplx<T>);
   if (sh.variant >= 4) {
-    // x-line taps for this window capacity (rebuilt when it changes)
+    // x-line taps for this mesh and window capacity (rebuilt when they change)
     if (vscratch) {
-      hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, c->d_v64, (cplx<T>*)vscratch, N, WC);
+      hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, v64, (cplx<T>*)vscratch, N, WC);
     } else {
-      int& have = fp64 ? c->xtaps_wc64 : c->xtaps_wc32;
+      const int key = N << 8 | WC;
+      int& have = fp64 ? c->xtaps_key64 : c->xtaps_key32;
       void*& own = fp64 ? c->d_xtaps64 : c->d_xtaps32;
-      if (have != WC || !own) {
-        if (own && have != WC) {
-          dev_free(c, own);
-          own = nullptr;
-        }
-        if (!own) {
-          pw_status s = dev_alloc(c, taps_bytes, &own);
-          if (s != PW_OK) return s;
-        }
-        hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, c->d_v64, (cplx<T>*)own, N, WC);
-        have = WC;
+      if (have != key || !own) {
+        dev_free(c, own);
+        own = nullptr;
+        pw_status s = dev_alloc(c, taps_bytes, &own);
+        if (s != PW_OK) return s;
+        hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, v64, (cplx<T>*)own, N, WC);
+        have = key;
       }
       vp = own;
     }
   } else if (vscratch) {
     hipLaunchKernelGGL(permute_v_kernel<T>, dim3(64), dim3(256), 0, st, v, (T*)vscratch, N, l3c);
   } else {
-    // permuted potential for this slab width (rebuilt when the width changes)
-    int& have = fp64 ? c->vperm_l3c64 : c->vperm_l3c32;
+    // permuted potential for this mesh and slab width (rebuilt when they change)
+    const int key = N << 8 | l3c;
+    int& have = fp64 ? c->vperm_key64 : c->vperm_key32;
     void*& own = fp64 ? c->d_vperm64 : c->d_vperm32;
-    if (have != l3c || !own) {
+    if (have != key || !own) {
+      if (have >> 8 != N) {
+        dev_free(c, own);
+        own = nullptr;
+      }
       if (!own) {
         pw_status s = dev_alloc(c, (size_t)N * N * N * sizeof(T), &own);
         if (s != PW_OK) return s;
       }
       hipLaunchKernelGGL(permute_v_kernel<T>, dim3(64), dim3(256), 0, st, v, (T*)own, N, l3c);
-      have = l3c;
+      have = key;
     }
     vp = own;
   }

@@ -136,10 +136,10 @@ struct pw_ctx {
   float* d_v32 = nullptr;
   void* d_vperm64 = nullptr;  // V/N_r permuted for the kernel's slab width
   void* d_vperm32 = nullptr;
-  int vperm_l3c64 = 0, vperm_l3c32 = 0;
+  int vperm_key64 = 0, vperm_key32 = 0;  // mesh and slab width they are laid out for
   void* d_xtaps64 = nullptr;  // x-line convolution taps of V/N_r for a window capacity
   void* d_xtaps32 = nullptr;
-  int xtaps_wc64 = 0, xtaps_wc32 = 0;
+  int xtaps_key64 = 0, xtaps_key32 = 0;  // mesh and window capacity
   int nproj = 0;
   void* d_beta64 = nullptr;  // (nk, nproj, npwx) complex double
   void* d_beta32 = nullptr;  // complex float
@@ -150,6 +150,12 @@ struct pw_ctx {
   void* d_q64 = nullptr;     // (nproj, nproj) complex double
   void* d_q32 = nullptr;     // complex float
   std::vector<double> qij;   // host copy, complex interleaved
+  // mesh of the autotuned H|psi> transforms (hpsi_potential.hip): the smallest
+  // compiled one that holds every Miller difference of the window, where that is
+  // below the context's mesh (else 0), and V on it divided by its size
+  int kmesh = 0;
+  void* d_vk64 = nullptr;  // double
+  void* d_vk32 = nullptr;  // float
 
   mkpw::KTables tables() const;
 };
@@ -169,6 +175,11 @@ pw_status host_pinned(pw_ctx* c, size_t bytes, void** out);
 pw_status launch_hpsi(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi,
                       hipStream_t stream, void* vscratch = nullptr);
 pw_status hpsi_scratch_init(pw_ctx* c);
+// what the H|psi> kernels read of the potential besides V itself, for this
+// context's V and k-list (called when either is set; nothing until both are)
+void hpsi_potential_build(pw_ctx* c);
+// smallest compiled mesh of at least n points per axis, 0 if there is none
+int hpsi_mesh_at_least(int n);
 bool hpsi_supported(int n1, int n2, int n3);
 
 // S|psi> = psi + sum_pq beta_p q_pq <beta_q|psi> over the selected vectors
