@@ -111,7 +111,8 @@ pw_status pw_set_option(pw_ctx* ctx, const char* key, int64_t value);
 
 /* Read an option (the keys above), or "hpsi_variant_tuned" / "hpsi_slab_tuned" /
  * "hpsi_threads_tuned" (the shape of this context's last H|psi> launch, 0 if
- * none), "device_bytes" (device memory the context holds now), "overlap"
+ * none; variant 6 is the local term as a dense product on the matrix cores,
+ * which launches without an explicit shape take where it is the faster one), "device_bytes" (device memory the context holds now), "overlap"
  * (1 while overlap coefficients q are set, else 0), or the context's sizes:
  * "nk" and "npwx" (0 before pw_set_kpoints), "nproj" (0 without projectors),
  * "fft1", "fft2", "fft3" (the mesh; 0 before pw_set_cutoff), and what the
@@ -194,7 +195,8 @@ pw_status pw_h_psi(pw_ctx* ctx, pw_prec prec, int nbnd, const void* psi, void* h
  * the potential (V permuted for its slab width, or the taps of its x-line
  * convolutions) is staged in a fixed array of the library (808 704 bytes, one
  * per GPU, held until the process ends; PW_EINVAL for a mesh that needs
- * more), rebuilt on every call.  The launch shape is the one
+ * more), rebuilt on every call; a launch that takes the dense product (variant
+ * 6) reads what the context holds and leaves the array alone.  The launch shape is the one
  * pw_h_psi has tuned for this mesh and batch size if it has, else a fixed
  * default (no tuning).  Every call on one GPU shares that GPU's array:
  * calls that overlap on one GPU (different streams or threads) race. */

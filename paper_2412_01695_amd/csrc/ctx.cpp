@@ -181,7 +181,7 @@ void clear_q(pw_ctx* c) {
 void free_kdata(pw_ctx* c) {
   for (void** p : {(void**)&c->d_npw, (void**)&c->d_nstick, (void**)&c->d_gmap, (void**)&c->d_sof,
                    (void**)&c->d_kin, (void**)&c->d_mkey, (void**)&c->d_lexperm, (void**)&c->d_beta64,
-                   (void**)&c->d_beta32, &c->d_vk64, &c->d_vk32}) {
+                   (void**)&c->d_beta32, &c->d_vk64, &c->d_vk32, &c->d_box64, &c->d_box32}) {
     dev_free(c, *p);
     *p = nullptr;
   }
@@ -592,6 +592,7 @@ pw_status pw_set_kpoints(pw_ctx* c, int nk, const double* k, int32_t* npw_out, i
     }
   }
   c->smax = smax;
+  c->npwmax = npwmax;
   if (npw_out)
     for (int ik = 0; ik < nk; ++ik) npw_out[ik] = c->npw[ik];
   if (npwx_out) *npwx_out = npwx;

@@ -99,6 +99,7 @@ pw_status launch_hpsi(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* ps
     return set_err(c, PW_EINVAL,
                    "unsupported FFT mesh " + std::to_string(c->fft[0]) + "x" + std::to_string(c->fft[1]) + "x" +
                        std::to_string(c->fft[2]) + " (cubic 15, 18, 20, 24, 30, 32, 36)");
+  if (hpsi_takes_dense(c, prec, sel)) return launch_hpsi_dense(c, prec, sel, psi, hpsi, st);
   if (prec == PW_FP64) return launch_t<double>(c, sel, psi, hpsi, st, vscratch);
   return launch_t<float>(c, sel, psi, hpsi, st, vscratch);
 }

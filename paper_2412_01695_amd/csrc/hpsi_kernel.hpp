@@ -873,10 +873,17 @@ pw_status launch_one(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, 
   // small launches, and launches that may not allocate (the tuning times
   // candidates with events and builds their potentials), take a fixed shape
   if ((long)t.nk * sel.nvec < kTuneMinRows || vscratch) {
+    // (x lines as convolutions with one work-item per line; over 2 to 64 k x 8 to
+    // 24 vectors within 5% of the best of every shape on each mesh at 256
+    // work-items below 30^3 and 512 from there; 52 Ry at 30^3, 64 k x 24 vectors:
+    // 145 us against 210 for lane pairs, the best variant without the convolution
+    // 170)
     HpsiShape sh;
-    sh.variant = (N % 2 == 0 && N >= 30) ? 2 : 1;
-    sh.threads = sh.variant == 2 ? 512 : 256;
-    sh.l3c = std::min(N, std::max(1, sh.threads / ((sh.variant == 2 ? 2 : 1) * N)));
+    sh.variant = WC < N ? 4 : (N % 2 == 0 && N >= 30) ? 2 : 1;
+    sh.threads = N >= 30 ? 512 : 256;
+    const int lanes = sh.variant == 2 ? 2 : 1;
+    if (!hpsi_kernel_ptr<T, N, WC>(sh)) sh.threads = 256;
+    sh.l3c = std::min(N, std::max(1, sh.threads / (lanes * N)));
     while (sh.l3c > 1 && hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) > kLdsPerCu / 2) --sh.l3c;
     if (!fits(sh)) return set_err(c, PW_EINVAL, "H|psi> working set does not fit in LDS for this mesh");
     return launch_shape<T, N, WC>(c, sel, psi, hpsi, st, sh, vscratch);

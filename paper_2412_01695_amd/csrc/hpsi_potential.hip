@@ -93,33 +93,50 @@ __global__ __launch_bounds__(256) void real_part_kernel(const cd* __restrict__ i
   }
 }
 
+// the upper half of the box (linear offsets >= 0 from its centre; V~(-d) = conj
+// V~(d)) in both precisions
+__global__ __launch_bounds__(256) void half_box_kernel(const cd* __restrict__ in, long n, cd* __restrict__ o64,
+                                                       cplx<float>* __restrict__ o32) {
+  for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
+    o64[e] = in[e];
+    o32[e] = {(float)in[e].x, (float)in[e].y};
+  }
+}
+
 dim3 grid_of(long total) { return dim3((unsigned)std::min<long>(4096, (total + 255) / 256)); }
 
 }  // namespace
 
 void hpsi_potential_build(pw_ctx* c) {
   if (c->host_only || !c->have_k || !c->have_v) return;
-  for (void** p : {&c->d_vk64, &c->d_vk32}) {
-    dev_free(c, *p);
-    *p = nullptr;
-  }
+  void** const kept[] = {&c->d_vk64, &c->d_vk32, &c->d_box64, &c->d_box32};
+  auto drop = [&]() {
+    for (void** p : kept) {
+      dev_free(c, *p);
+      *p = nullptr;
+    }
+  };
+  drop();
   c->kmesh = 0;
   c->vperm_key64 = c->vperm_key32 = 0;  // copies made for the kernels are rebuilt
   c->xtaps_key64 = c->xtaps_key32 = 0;
   const int n = c->fft[0];
   if (!hpsi_supported(c->fft[0], c->fft[1], c->fft[2])) return;
   const int w[3] = {c->wx, c->wy, c->wz};
-  const int m = hpsi_mesh_at_least(2 * std::max(w[0], std::max(w[1], w[2])) - 1);
-  if (m == 0 || m >= n) return;
+  int m = hpsi_mesh_at_least(2 * std::max(w[0], std::max(w[1], w[2])) - 1);
+  if (m >= n) m = 0;
+  const long half = hpsi_dense_box(c);
+  if (m == 0 && half == 0) return;
   const long d1 = 2 * w[0] - 1, d2 = 2 * w[1] - 1, d3 = 2 * w[2] - 1, nr = (long)m * m * m;
-  // two work arrays for the passes; without memory for them or for V the
-  // context keeps its own mesh
+  // two work arrays for the passes; without memory for them or for what is kept
+  // the context has its own mesh alone
   const std::string err = c->err;
   const long most = std::max({d1 * n * n, d1 * d2 * n, d1 * d2 * d3, nr});
   void *a = nullptr, *b = nullptr;
-  bool ok = dev_alloc(c, sizeof(cd) * most, &a) == PW_OK && dev_alloc(c, sizeof(cd) * most, &b) == PW_OK &&
-            dev_alloc(c, sizeof(double) * nr, &c->d_vk64) == PW_OK &&
-            dev_alloc(c, sizeof(float) * nr, &c->d_vk32) == PW_OK;
+  auto get = [&](long bytes, void** p) { return dev_alloc(c, (size_t)bytes, p) == PW_OK; };
+  bool ok = get(sizeof(cd) * most, &a) && get(sizeof(cd) * most, &b) && get(sizeof(double) * nr, &c->d_vk64) &&
+            get(sizeof(float) * nr, &c->d_vk32) && get(sizeof(cd) * half, &c->d_box64) &&
+            get(sizeof(cplx<float>) * half, &c->d_box32);
   if (ok) {
     cd *x = (cd*)a, *y = (cd*)b;
     const dim3 wg(256);
@@ -127,24 +144,26 @@ void hpsi_potential_build(pw_ctx* c) {
     hipLaunchKernelGGL(to_box_kernel<double>, grid_of(d1 * n * n), wg, 0, st, c->d_v64, x, 1, n, n * n, w[0]);
     hipLaunchKernelGGL(to_box_kernel<cd>, grid_of(d1 * d2 * n), wg, 0, st, x, y, (int)d1, n, n, w[1]);
     hipLaunchKernelGGL(to_box_kernel<cd>, grid_of(d1 * d2 * d3), wg, 0, st, y, x, (int)(d1 * d2), n, 1, w[2]);
-    hipLaunchKernelGGL(from_box_kernel, grid_of(d1 * d2 * m), wg, 0, st, x, y, (int)(d1 * d2), m, 1, w[2]);
-    hipLaunchKernelGGL(from_box_kernel, grid_of(d1 * m * m), wg, 0, st, y, x, (int)d1, m, m, w[1]);
-    hipLaunchKernelGGL(from_box_kernel, grid_of(nr), wg, 0, st, x, y, 1, m, m * m, w[0]);
-    hipLaunchKernelGGL(real_part_kernel, grid_of(nr), wg, 0, st, y, nr, 1.0 / (double)nr, (double*)c->d_vk64,
-                       (float*)c->d_vk32);
+    if (half)
+      hipLaunchKernelGGL(half_box_kernel, grid_of(half), wg, 0, st, x + d1 * d2 * d3 - half, half, (cd*)c->d_box64,
+                         (cplx<float>*)c->d_box32);
+    if (m) {
+      hipLaunchKernelGGL(from_box_kernel, grid_of(d1 * d2 * m), wg, 0, st, x, y, (int)(d1 * d2), m, 1, w[2]);
+      hipLaunchKernelGGL(from_box_kernel, grid_of(d1 * m * m), wg, 0, st, y, x, (int)d1, m, m, w[1]);
+      hipLaunchKernelGGL(from_box_kernel, grid_of(nr), wg, 0, st, x, y, 1, m, m * m, w[0]);
+      hipLaunchKernelGGL(real_part_kernel, grid_of(nr), wg, 0, st, y, nr, 1.0 / (double)nr, (double*)c->d_vk64,
+                         (float*)c->d_vk32);
+    }
     ok = hipGetLastError() == hipSuccess;
   }
   dev_free(c, a);
   dev_free(c, b);
   if (ok) {
     c->kmesh = m;
-    return;
+  } else {
+    drop();
+    c->err = err;
   }
-  for (void** p : {&c->d_vk64, &c->d_vk32}) {
-    dev_free(c, *p);
-    *p = nullptr;
-  }
-  c->err = err;
 }
 
 }  // namespace mkpw

@@ -156,6 +156,11 @@ struct pw_ctx {
   int kmesh = 0;
   void* d_vk64 = nullptr;  // double
   void* d_vk32 = nullptr;  // float
+  // V~ at the window's Miller differences (the half of them with a linear offset
+  // >= 0; hpsi_dense.hip), null where it does not fit the kernels
+  void* d_box64 = nullptr;  // complex double
+  void* d_box32 = nullptr;  // complex float
+  int npwmax = 0;           // largest npw
 
   mkpw::KTables tables() const;
 };
@@ -178,6 +183,12 @@ pw_status hpsi_scratch_init(pw_ctx* c);
 // what the H|psi> kernels read of the potential besides V itself, for this
 // context's V and k-list (called when either is set; nothing until both are)
 void hpsi_potential_build(pw_ctx* c);
+// H|psi> with the local term as a dense product (hpsi_dense.hip): entries of the
+// box it reads (0: too wide), whether it takes a call, the launch
+int hpsi_dense_box(const pw_ctx* c);
+bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel);
+pw_status launch_hpsi_dense(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi,
+                            hipStream_t stream);
 // smallest compiled mesh of at least n points per axis, 0 if there is none
 int hpsi_mesh_at_least(int n);
 bool hpsi_supported(int n1, int n2, int n3);
