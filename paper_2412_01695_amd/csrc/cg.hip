@@ -32,6 +32,7 @@
 
 #include "host_util.hpp"
 #include "internal.hpp"
+#include "wave.hpp"
 
 namespace mkpw {
 
@@ -181,6 +182,116 @@ __global__ __launch_bounds__(256) void step2_kernel(cd* t, const cd* d, cd* dold
   if (threadIdx.x == 0) rho_old[sys] = rho[sys];
 }
 
+// Steps 2 and 1 of one system in one pass, its rows in registers (E values per
+// lane, NWV waves per system, rows of at most 64 E NWV): every array is read and
+// written once (four reads, three writes; the two kernels apart make eight and
+// five), d is updated in place and neither t nor the last d is written back.
+// HBM-bound: 2048 k x 8 systems, npwx 320, 587 MB in 78 us (7.5 TB/s, part of it
+// from the last-level cache); the two kernels apart took 161 us.
+template <int E, int NWV>
+__global__ __launch_bounds__(256) void step_kernel(const cd* __restrict__ t, cd* __restrict__ d, cd* __restrict__ x,
+                                                   cd* __restrict__ r, const double* __restrict__ eps,
+                                                   const double* __restrict__ kin, const double* __restrict__ tk,
+                                                   const int* __restrict__ npw, int npwx, int nrhs, long nsys,
+                                                   double* rho, const double* __restrict__ rho0, int* active,
+                                                   int sub_eps, double thr, double rel, int* iters) {
+  __shared__ double red[3][4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const long sys = NWV == 1 ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
+  if (sys >= nsys || !active[sys]) return;  // the same for all waves of a system
+  const int k = (int)(sys / nrhs), n = npw[k];
+  const long o = sys * npwx;
+  const int g0 = NWV == 1 ? lane : (int)threadIdx.x;
+  auto total = [&](double v, int slot) {
+    v = wave_sum(v);
+    if constexpr (NWV > 1) {
+      if (lane == 0) red[slot][wave] = v;
+      __syncthreads();
+      v = (red[slot][0] + red[slot][1]) + (red[slot][2] + red[slot][3]);
+    }
+    return v;
+  };
+  const double e = sub_eps ? eps[sys] : 0.0, tkin = tk[sys], rho_old = rho[sys];
+  cd tv[E], dv[E], rv[E], xv[E];
+  double kv[E];
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int g = g0 + u * 64 * NWV, h = g < n ? g : 0;
+    tv[u] = t[o + h];
+    dv[u] = d[o + h];
+    rv[u] = r[o + h];
+    xv[u] = x[o + h];
+    kv[u] = kin[(long)k * npwx + h];
+  }
+  double dr = 0.0, dt = 0.0;
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    if (g0 + u * 64 * NWV < n) {
+      tv[u] = {tv[u].x - e * dv[u].x, tv[u].y - e * dv[u].y};
+      dr += dv[u].x * rv[u].x + dv[u].y * rv[u].y;
+      dt += dv[u].x * tv[u].x + dv[u].y * tv[u].y;
+    }
+  }
+  dr = total(dr, 0);
+  dt = total(dt, 1);
+  const double lam = -dr / dt;
+  cd v[E];
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int g = g0 + u * 64 * NWV;
+    if (g < n) {
+      x[o + g] = {xv[u].x + lam * dv[u].x, xv[u].y + lam * dv[u].y};
+      rv[u] = {rv[u].x + lam * tv[u].x, rv[u].y + lam * tv[u].y};
+      r[o + g] = rv[u];
+      const double m = fmax(1.0, kv[u] / tkin);
+      v[u] = {rv[u].x / m, rv[u].y / m};
+      s += v[u].x * rv[u].x + v[u].y * rv[u].y;
+    }
+  }
+  s = total(s, 2);
+  const bool first = g0 == 0;
+  if (first) rho[sys] = s;
+  if (fabs(s) < fmax(thr, rel * fabs(rho0[sys]))) {
+    if (first) active[sys] = 0;
+    return;
+  }
+  const double gam = s / rho_old;
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int g = g0 + u * 64 * NWV;
+    if (g < n) d[o + g] = {v[u].x + gam * dv[u].x, v[u].y + gam * dv[u].y};
+  }
+  if (first) iters[sys] += 1;  // one more update for this system
+}
+
+constexpr int kStepMax = 2048;  // longest rows step_kernel holds
+
+void launch_step(int npwx, long nsys, hipStream_t st, const cd* t, cd* d, cd* x, cd* r, const double* eps,
+                 const double* kin, const double* tk, const int* npw, int nrhs, double* rho, const double* rho0,
+                 int* active, int sub_eps, double thr, double rel, int* iters) {
+#define MKPW_STEP(E, NWV)                                                                                       \
+  hipLaunchKernelGGL((step_kernel<E, NWV>), dim3((unsigned)(NWV == 1 ? (nsys + 3) / 4 : nsys)), dim3(256), 0, st, t, d, \
+                     x, r, eps, kin, tk, npw, npwx, nrhs, nsys, rho, rho0, active, sub_eps, thr, rel, iters)
+  // one wave per system up to 512 plane waves (no barriers), else four
+  switch (npwx <= 512 ? npwx / 64 : 100 + (npwx + 255) / 256) {
+    case 1: MKPW_STEP(1, 1); break;
+    case 2: MKPW_STEP(2, 1); break;
+    case 3: MKPW_STEP(3, 1); break;
+    case 4: MKPW_STEP(4, 1); break;
+    case 5: MKPW_STEP(5, 1); break;
+    case 6: MKPW_STEP(6, 1); break;
+    case 7: MKPW_STEP(7, 1); break;
+    case 8: MKPW_STEP(8, 1); break;
+    case 103: MKPW_STEP(3, 4); break;
+    case 104: MKPW_STEP(4, 4); break;
+    case 105:
+    case 106: MKPW_STEP(6, 4); break;
+    default: MKPW_STEP(8, 4); break;
+  }
+#undef MKPW_STEP
+}
+
 }  // namespace
 
 
@@ -197,7 +308,9 @@ pw_status dfpt_cg_run(pw_ctx* c, pw_prec prec, int nocc, const cd* U, const doub
   int* active;
   MKPW_TRY(bf.get(nv, &r));
   MKPW_TRY(bf.get(nv, &d));
-  MKPW_TRY(bf.get(nv, &dold));
+  const bool fused = npwx <= kStepMax;  // both steps in one kernel, d in place
+  dold = nullptr;
+  if (!fused) MKPW_TRY(bf.get(nv, &dold));
   MKPW_TRY(bf.get(nv, &t));
   MKPW_TRY(bf.get((size_t)nk * nocc * nrhs, &W));
   MKPW_TRY(bf.get((size_t)nsys, &eps));
@@ -215,7 +328,7 @@ pw_status dfpt_cg_run(pw_ctx* c, pw_prec prec, int nocc, const cd* U, const doub
   }
   MKPW_HIP(c, hipMemcpyAsync(eps, eps_h, sizeof(double) * nsys, hipMemcpyHostToDevice, st));
   MKPW_HIP(c, hipMemcpyAsync(alpha, alpha_h, sizeof(double) * nk, hipMemcpyHostToDevice, st));
-  MKPW_HIP(c, hipMemsetAsync(dold, 0, sizeof(cd) * nv, st));
+  if (!fused) MKPW_HIP(c, hipMemsetAsync(dold, 0, sizeof(cd) * nv, st));
   MKPW_HIP(c, hipMemsetAsync(rho_old, 0, sizeof(double) * nsys, st));
   hipLaunchKernelGGL(tkin_kernel, dim3(nrhs, nk), dim3(256), 0, st, U, nocc, c->d_kin, c->d_npw, npwx, nrhs, tk);
   MKPW_TRY(check_launch(c, "tkin", st));
@@ -241,7 +354,17 @@ pw_status dfpt_cg_run(pw_ctx* c, pw_prec prec, int nocc, const cd* U, const doub
     sel.nvec = nrhs;
     sel.kstride = (long)nrhs * npwx;
     sel.live = live;
-    if (fp64_h) {
+    // in FP64 the projector term goes into the dense H|psi> product, as more
+    // projectors (2048 k x 8 systems, 8 occupied bands: the Gram and combine
+    // kernels it replaces took 105 us of 560 a unit)
+    const bool folded = fp64_h && hpsi_takes_dense(c, PW_FP64, sel, nocc);
+    if (folded) {
+      ProjTerm pv;
+      pv.rows = P;
+      pv.n = nocc;
+      pv.alpha = alpha;
+      MKPW_TRY(launch_hpsi_dense(c, PW_FP64, sel, v, t, st, &pv));
+    } else if (fp64_h) {
       MKPW_TRY(launch_hpsi(c, PW_FP64, sel, v, t, st));
     } else {
       MKPW_TRY(
@@ -251,6 +374,7 @@ pw_status dfpt_cg_run(pw_ctx* c, pw_prec prec, int nocc, const cd* U, const doub
           launch_to_c128(c, t32, (long)nrhs * npwx, nullptr, t, (long)nrhs * npwx, nullptr, nullptr, nrhs, st, live));
     }
     if (gen) MKPW_TRY(launch_spsi(c, PW_FP64, sel, v, t, eps, -1.0, st));  // t -= eps S v
+    if (folded) return PW_OK;
     GramArgs g;
     g.A = P; g.a_kstride = (long)nocc * npwx; g.a_n = nocc;
     g.B = v; g.b_kstride = (long)nrhs * npwx; g.b_n = nrhs;
@@ -318,21 +442,31 @@ pw_status dfpt_cg_run(pw_ctx* c, pw_prec prec, int nocc, const cd* U, const doub
     graph = nullptr;
   };
 
-  auto step1 = [&](int first) -> pw_status {
-    // the FP32 phase of the mixed mode stops at a residual reduction its
-    // H application can still resolve; the FP64 phase runs to thr
-    // rho reduction (squared M^-1-norm of the residual) at which the mixed
-    // mode leaves complex64 H: by default 1e-10, a residual norm 1e-5 of the
-    // starting one, near what an H application with FP32 rounding resolves
-    const double rel = fp64_h ? 0.0 : std::pow(10.0, -(double)c->cg_switch_digits);
-    hipLaunchKernelGGL(step1_kernel, dim3((unsigned)nsys), dim3(256), 0, st, r, d, dold, c->d_kin, tk, c->d_npw, npwx,
-                       nrhs, rho, rho_old, rho0, active, first, thr, rel, iters_d);
-    MKPW_TRY(check_launch(c, "cg_step1", st));
+  auto count = [&]() -> pw_status {
     hipLaunchKernelGGL(count_active_kernel, dim3(1), dim3(1024), 0, st, active, nsys, d_nact);
     return check_launch(c, "count_active", st);
   };
+  // the FP32 phase of the mixed mode stops at a residual reduction its H
+  // application can still resolve; the FP64 phase runs to thr
+  // rho reduction (squared M^-1-norm of the residual) at which the mixed
+  // mode leaves complex64 H: by default 1e-10, a residual norm 1e-5 of the
+  // starting one, near what an H application with FP32 rounding resolves
+  auto phase_rel = [&]() { return fp64_h ? 0.0 : std::pow(10.0, -(double)c->cg_switch_digits); };
+  auto step1 = [&](int first) -> pw_status {
+    const double rel = phase_rel();
+    hipLaunchKernelGGL(step1_kernel, dim3((unsigned)nsys), dim3(256), 0, st, r, d, dold, c->d_kin, tk, c->d_npw, npwx,
+                       nrhs, rho, rho_old, rho0, active, first, thr, rel, iters_d);
+    MKPW_TRY(check_launch(c, "cg_step1", st));
+    return count();
+  };
   auto unit = [&]() -> pw_status {
     MKPW_TRY(apply_a(d, active));
+    if (fused) {
+      launch_step(npwx, nsys, st, t, d, x, r, eps, c->d_kin, tk, c->d_npw, nrhs, rho, rho0, active, gen ? 0 : 1, thr,
+                  phase_rel(), iters_d);
+      MKPW_TRY(check_launch(c, "cg_step", st));
+      return count();
+    }
     hipLaunchKernelGGL(step2_kernel, dim3((unsigned)nsys), dim3(256), 0, st, t, d, dold, x, r, eps, c->d_npw, npwx,
                        nrhs, rho, rho_old, active, gen ? 0 : 1);
     MKPW_TRY(check_launch(c, "cg_step2", st));

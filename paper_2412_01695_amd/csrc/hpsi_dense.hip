@@ -129,6 +129,10 @@ struct DenseArgs {
   int nproj;
   const cplx<T>* beta;
   const cplx<T>* dij;
+  // projectors nproj .. nproj + nextra - 1: rows of a term alpha_k |row> <row|
+  int nextra;
+  const cplx<T>* extra;
+  const double* alpha;
   const cplx<T>* box;  // V~ of the Miller differences of linear offset 0 .. nhalf - 1
   int s2, s3, nhalf;   // strides of the box
   const cplx<T>* psi;
@@ -151,10 +155,10 @@ struct DenseLds {
   size_t buf, dl, wcol, slot, bytes;
 };
 template <class T>
-__host__ __device__ constexpr DenseLds dense_lds(int nw, int ngm, int rt, int npwx, int nhalf, int nproj) {
+__host__ __device__ constexpr DenseLds dense_lds(int nw, int ngm, int rt, int npwx, int nhalf, int nproj, int nall) {
   const size_t cs = sizeof(cplx<T>), nb = 8 * (size_t)ngm;
   const size_t box = ((size_t)nhalf * cs + 15) / 16 * 16, buf = 2 * nb * dense_bs<T>(nw, ngm, rt) * sizeof(T);
-  const size_t proj = nproj > 0 ? ((size_t)nw * 16 + 16 + kGS) * nb * cs : 0, tile = (size_t)nw * nb * kTS * cs;
+  const size_t proj = nall > 0 ? ((size_t)nw * 16 + 16 + kGS) * nb * cs : 0, tile = (size_t)nw * nb * kTS * cs;
   size_t work = box + buf;
   if (proj > work) work = proj;
   if (tile > work) work = tile;
@@ -183,8 +187,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   constexpr int kAhead = NGM == 1 && RTM > 2 ? 2 : 1;
   constexpr int kL = (kSteps + NW - 1) / NW;  // steps of a chunk that a wave sums for the projectors
   extern __shared__ __align__(16) char smem[];
-  const int npwx = a.npwx, nproj = a.nproj;
-  const DenseLds L = dense_lds<T>(NW, NGM, RTM, npwx, a.nhalf, nproj);
+  const int npwx = a.npwx, nproj = a.nproj, nall = nproj + a.nextra;
+  const DenseLds L = dense_lds<T>(NW, NGM, RTM, npwx, a.nhalf, nproj, nall);
   T* buf = reinterpret_cast<T*>(smem + L.buf);  // [2][NB][BS]
   int* wcol = reinterpret_cast<int*>(smem + L.wcol);  // byte offset of each column G, past npw that of G = 0
   int* slot = reinterpret_cast<int*>(smem + L.slot);  // [NB] the selected vectors, then their number
@@ -303,7 +307,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
     for (int i = 0; i < RTM; ++i) acc[g][i] = acc_t{0, 0, 0, 0};
   }
-  const cplx<T>* brow = a.beta + ((long)ik * nproj + (l16 < nproj ? l16 : 0)) * npwx;
+  // row p of the k's projectors, both kinds
+  auto proj_row = [&](int p) {
+    return p < nproj ? a.beta + ((long)ik * nproj + p) * npwx : a.extra + ((long)ik * a.nextra + p - nproj) * npwx;
+  };
+  const cplx<T>* brow = nall > 0 ? proj_row(l16 < nall ? l16 : 0) : nullptr;
   // the sum over G for NF full groups and NQ sets of the next one (the same for
   // the whole workgroup, so that the steps of a chunk are straight-line code);
   // set t of group NF is summed in component t of that group's accumulators
@@ -331,10 +339,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     int w = wcol[4 * AH + kq];  // of the next entry to read
     // projector overlaps lambda = beta^H psi (Eq. lambdah), rows = projectors:
     // the steps are dealt to the waves
-    auto mine = [&](int c) { return nproj > 0 && (kSteps >= NW || (c & (NW / kSteps - 1)) == wave / kSteps); };
+    auto mine = [&](int c) { return nall > 0 && (kSteps >= NW || (c & (NW / kSteps - 1)) == wave / kSteps); };
     auto first_step = [&]() { return kSteps >= NW ? wave : wave & (kSteps - 1); };
     auto load_beta = [&](int c, cplx<T>(&x)[kL]) {
-      if (nproj > 0 && c < nch) {
+      if (nall > 0 && c < nch) {
 #pragma unroll
         for (int u = 0; u < kL; ++u) {
           const int j = c * KC + 4 * (first_step() + NW * u) + kq;
@@ -410,7 +418,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
         const int ls0 = first_step();
 #pragma unroll
         for (int u = 0; u < kL; ++u) {
-          const T lx = l16 < nproj ? bl[u].x : T(0), ly = l16 < nproj ? -bl[u].y : T(0);
+          const T lx = l16 < nall ? bl[u].x : T(0), ly = l16 < nall ? -bl[u].y : T(0);
           Col x[NG];
           load_b(x, ls0 + NW * u);
 #pragma unroll
@@ -471,15 +479,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
   // gamma = D lambda (Eq. gamma), then sum_p beta_p gamma_p (Eq. finalnl) as
   // more columns of the same product
-  if (nproj > 0) {
-    const cplx<T>* bk = a.beta + (long)ik * nproj * npwx;
+  if (nall > 0) {
     cplx<T> x[RTM];
     auto beta_rows = [&](int p0) {
-      const int p = p0 + kq;
+      const cplx<T>* pr = proj_row(p0 + kq < nall ? p0 + kq : 0);
 #pragma unroll
       for (int i = 0; i < RTM; ++i) {
         const int g = (t0 + i * tstep) * 16 + l16;
-        x[i] = bk[g < npw && p < nproj ? (long)p * npwx + g : 0];
+        x[i] = pr[g < npw ? g : 0];
       }
     };
     beta_rows(0);
@@ -504,20 +511,24 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     for (int e = tid; e < 16 * NB; e += NT) {
       const int b = e >> 4, p = e & 15;
       cplx<T> y = {T(0), T(0)};
-      if (p < nproj)
+      if (p < nproj) {
         for (int q = 0; q < nproj; ++q) y = cfma(dl[p * nproj + q], ls[q * NB + b], y);
+      } else if (p < nall) {
+        const T al = (T)a.alpha[ik];
+        y = {al * ls[p * NB + b].x, al * ls[p * NB + b].y};
+      }
       gs[b * kGS + p] = y;
     }
     __syncthreads();
-    for (int p0 = 0; p0 < nproj; p0 += 4) {
+    for (int p0 = 0; p0 < nall; p0 += 4) {
       const int p = p0 + kq;
       cplx<T> y[RTM];
 #pragma unroll
       for (int i = 0; i < RTM; ++i) {
-        const bool ok = (t0 + i * tstep) * 16 + l16 < npw && p < nproj;
+        const bool ok = (t0 + i * tstep) * 16 + l16 < npw && p < nall;
         y[i] = {ok ? x[i].x : T(0), ok ? x[i].y : T(0)};
       }
-      if (p0 + 4 < nproj) beta_rows(p0 + 4);
+      if (p0 + 4 < nall) beta_rows(p0 + 4);
 #pragma unroll
       for (int g = 0; g < NGM; ++g) {
         if (g < nfull) {
@@ -609,7 +620,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 template <class T, int NW, int NGM, int RTM>
 pw_status launch_inst(pw_ctx* c, DenseArgs<T>& a, hipStream_t st) {
-  const size_t lds = dense_lds<T>(NW, NGM, RTM, a.npwx, a.nhalf, a.nproj).bytes;
+  const size_t lds = dense_lds<T>(NW, NGM, RTM, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra).bytes;
   const void* kern = (const void*)hpsi_dense_kernel<T, NW, NGM, RTM>;
   pw_status s = ensure_lds_limit(c, kern, lds);
   if (s != PW_OK) return s;
@@ -642,7 +653,7 @@ pw_status launch_ng(pw_ctx* c, DenseArgs<T>& a, int ngm, int rt, hipStream_t st)
 }
 
 template <class T>
-pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st) {
+pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st, const ProjTerm* extra) {
   const bool fp64 = sizeof(T) == 8;
   DenseArgs<T> a;
   a.npw = c->d_npw;
@@ -653,6 +664,9 @@ pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hi
   a.nproj = c->have_proj ? c->nproj : 0;
   a.beta = (const cplx<T>*)(fp64 ? c->d_beta64 : c->d_beta32);
   a.dij = (const cplx<T>*)(fp64 ? c->d_dij64 : c->d_dij32);
+  a.nextra = extra ? extra->n : 0;
+  a.extra = extra ? (const cplx<T>*)extra->rows : nullptr;
+  a.alpha = extra ? extra->alpha : nullptr;
   a.box = (const cplx<T>*)(fp64 ? c->d_box64 : c->d_box32);
   a.s2 = 2 * c->wy - 1;
   a.s3 = 2 * c->wz - 1;
@@ -662,7 +676,7 @@ pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hi
   if ((long)c->nk * sel.nvec <= 0) return PW_OK;
   const int groups = (sel.nvec + 7) / 8;
   const int tiles = std::max(1, (c->npwmax + 15) / 16);
-  auto lds = [&](int nw, int ngm, int rt) { return dense_lds<T>(nw, ngm, rt, a.npwx, a.nhalf, a.nproj).bytes; };
+  auto lds = [&](int nw, int ngm, int rt) { return dense_lds<T>(nw, ngm, rt, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra).bytes; };
   // as many vectors per workgroup as fit (each entry of the box that is read
   // serves them all); two workgroups of four waves per CU where two fit, else
   // one of eight
@@ -702,7 +716,7 @@ int hpsi_dense_box(const pw_ctx* c) {
   const long n = (long)(2 * c->wx - 1) * (2 * c->wy - 1) * (2 * c->wz - 1);
   const long half = (n + 1) / 2;
   if (half > (long)(kLdsPerCu / sizeof(cplx<double>))) return 0;
-  return dense_lds<double>(8, 1, 3, c->npwx, (int)half, kMaxProjDense).bytes <= kLdsPerCu ? (int)half : 0;
+  return dense_lds<double>(8, 1, 3, c->npwx, (int)half, kMaxProjDense, kMaxProjDense).bytes <= kLdsPerCu ? (int)half : 0;
 }
 
 // Whether H|psi> of this call takes the dense product rather than the transforms
@@ -719,10 +733,10 @@ int hpsi_dense_box(const pw_ctx* c) {
 //     two thirds at a time, 2266 / 2900; complex64, whose transforms take half
 //     the time of FP64 at a quarter of the issue slots: 1200 k x 16 [305] 268 /
 //     181, [469] 437 / 383, x 24 [576] 814 / 840.
-bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel) {
+bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel, int nextra) {
   if (!c->d_box64 || !c->d_box32) return false;
   if (c->hpsi_variant != 0 || c->hpsi_slab != 0 || c->hpsi_threads != 0) return false;  // a transform shape is asked for
-  if (c->have_proj && c->nproj > kMaxProjDense) return false;  // lambda is one tile of rows
+  if ((c->have_proj ? c->nproj : 0) + nextra > kMaxProjDense) return false;  // lambda is one tile of rows
   const int npw = c->npwmax, nk = c->nk, nv = sel.nvec;
   if (npw <= 128) return nv >= 3;
   if (nv < 6) return false;
@@ -736,8 +750,9 @@ bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel) {
   return npw <= 520 && nk >= 1024 && nv >= 14;
 }
 
-pw_status launch_hpsi_dense(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st) {
-  return prec == PW_FP64 ? launch_t<double>(c, sel, psi, hpsi, st) : launch_t<float>(c, sel, psi, hpsi, st);
+pw_status launch_hpsi_dense(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st,
+                            const ProjTerm* extra) {
+  return prec == PW_FP64 ? launch_t<double>(c, sel, psi, hpsi, st, extra) : launch_t<float>(c, sel, psi, hpsi, st, extra);
 }
 
 }  // namespace mkpw

@@ -33,4 +33,12 @@ struct VecSel {
   const int* live = nullptr;  // [nk * nvec] nonzero for rows to compute, or null (rows left unwritten)
 };
 
+// Projector term that an H|psi> launch may add beside the context's own: for k,
+// alpha[k] sum_p |row_p> <row_p|psi>, rows (nk, n, npwx).
+struct ProjTerm {
+  const void* rows = nullptr;  // complex of the launch's precision
+  int n = 0;
+  const double* alpha = nullptr;  // [nk], device
+};
+
 }  // namespace mkpw

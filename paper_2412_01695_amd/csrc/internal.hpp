@@ -186,9 +186,10 @@ void hpsi_potential_build(pw_ctx* c);
 // H|psi> with the local term as a dense product (hpsi_dense.hip): entries of the
 // box it reads (0: too wide), whether it takes a call, the launch
 int hpsi_dense_box(const pw_ctx* c);
-bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel);
+// (with `extra`, a projector term added to H; the transforms have no such term)
+bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel, int nextra = 0);
 pw_status launch_hpsi_dense(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi,
-                            hipStream_t stream);
+                            hipStream_t stream, const ProjTerm* extra = nullptr);
 // smallest compiled mesh of at least n points per axis, 0 if there is none
 int hpsi_mesh_at_least(int n);
 bool hpsi_supported(int n1, int n2, int n3);
