@@ -280,10 +280,11 @@ __global__ __launch_bounds__(kDvWaves * 64) void dvpsi_mfma_kernel(
 }
 
 constexpr int kRhoWaves = 16;  // waves per workgroup of drho_mfma_kernel
+constexpr int kDrhoWgs = 256;  // its workgroups that run at once, one per CU
 
 // Per k: bins F_k(d) += 4 w_k M(G1, G2) over the pairs with d = m_G2 - m_G1 -
 // org_k in the box [0, D1) x [0, D2) x [0, D3), for the slice x0 <= d1 < x0 +
-// nx held in LDS (written to part[k]), where M = U1^H U2 (sum over the bands
+// nx held in LDS (written to the workgroup's part), where M = U1^H U2 (sum over the bands
 // of conj(u1(G1)) u2(G2)) is formed on the matrix cores: each wave takes a
 // contiguous run of 16 x 16 tiles of (G1, G2), row by row, four bands per step
 // (with NBS > 0 the NBS steps of a tile row's U1 entries stay in registers
@@ -292,11 +293,13 @@ constexpr int kRhoWaves = 16;  // waves per workgroup of drho_mfma_kernel
 // atomics: the order of the additions into a bin varies from run to run, so
 // results agree to rounding, not bit for bit).  A bin's index is the box
 // offset of m_G2 less that of m_G1 less the k's origin, from per-G offsets
-// staged in LDS after the bins.  One workgroup per k; the bins fill most of a
-// CU's LDS, so a workgroup is as wide as a CU takes to hide latency.
+// staged in LDS after the bins.  The bins fill most of a CU's LDS, so a
+// workgroup is as wide as a CU takes to hide latency, and it keeps its bins for
+// all its units (run u % nrun of the tiles of k = u / nrun), the tables of the
+// next k filled under the tiles of this one.
 template <int NBS>
 __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
-    int nbnd, const double* __restrict__ wk, const int* __restrict__ npw1, const int* __restrict__ key1, int npwx1,
+    int nk, int nrun, int nbnd, const double* __restrict__ wk, const int* __restrict__ npw1, const int* __restrict__ key1, int npwx1,
     const cd* __restrict__ u1, const int* __restrict__ npw2, const int* __restrict__ key2, int npwx2,
     const cd* __restrict__ u2, const int* __restrict__ org, int D1, int D2, int D3, int x0, int nx,
     cd* __restrict__ part) {
@@ -305,126 +308,149 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
   const int nbin_al = (nbin + 1) & ~1;
   double* bre = reinterpret_cast<double*>(smem);
   double* bim = bre + nbin_al;
-  int* o1s = reinterpret_cast<int*>(bim + nbin_al);  // [npwx1]
-  int* o2s = o1s + npwx1;                            // [npwx2]
-  const int k = blockIdx.x;
+  int* o1s = reinterpret_cast<int*>(bim + nbin_al);  // [2][npwx1 + npwx2]
   // wave index made wave-uniform for the compiler, so that the tile walk runs
   // on the scalar unit
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) bre[e] = bim[e] = 0.0;
-  const int n1 = npw1[k], n2 = npw2[k];
-  for (int g = threadIdx.x; g < n1; g += kRhoWaves * 64) o1s[g] = miller_lin(key1[(long)k * npwx1 + g], D2, D3);
-  for (int g = threadIdx.x; g < n2; g += kRhoWaves * 64) o2s[g] = miller_lin(key2[(long)k * npwx2 + g], D2, D3);
-  __syncthreads();
-  const double f = 4.0 * wk[k];
-  const int base = ((org[3 * k] + x0) * D2 + org[3 * k + 1]) * D3 + org[3 * k + 2];
-  const int nit = (n1 + 15) / 16, njt = (n2 + 15) / 16, ntile = nit * njt;
-  const int l16 = lane & 15, kq = lane >> 4;
-  const int t0 = (int)((long)ntile * wave / kRhoWaves), t1 = (int)((long)ntile * (wave + 1) / kRhoWaves);
-  const cd* u1k = u1 + (long)k * nbnd * npwx1;
-  const cd* u2k = u2 + (long)k * nbnd * npwx2;
-  constexpr int NR = NBS > 0 ? NBS : 1;
-  // with the A entries in registers the weight f is folded into them
-  const double fb = NBS > 0 ? 1.0 : f;
-  double arc[NR], aic[NR], naic[NR], brc[NR], bic[NR];
-  int o1v[4];
-  // B entries of tile column jt (register path): unconditional loads from
-  // clamped addresses; a band past nbnd meets a zeroed A entry, and a column
-  // past the sphere is never binned
-  auto fetch_b = [&](int jt) {
-    const int g2 = jt * 16 + l16;
-    const cd* b2 = u2k + (g2 < n2 ? g2 : 0);
-#pragma unroll
-    for (int s = 0; s < NR; ++s) {
-      const int nu = 4 * s + kq;
-      const cd b = b2[(long)(nu < nbnd ? nu : 0) * npwx2];
-      brc[s] = b.x;
-      bic[s] = b.y;
-    }
+  // box offsets of the G of k-point kk into table buffer `which`
+  auto tables = [&](int kk, int which) {
+    int* t1 = o1s + which * (npwx1 + npwx2);
+    for (int g = threadIdx.x; g < npw1[kk]; g += kRhoWaves * 64) t1[g] = miller_lin(key1[(long)kk * npwx1 + g], D2, D3);
+    for (int g = threadIdx.x; g < npw2[kk]; g += kRhoWaves * 64)
+      t1[npwx1 + g] = miller_lin(key2[(long)kk * npwx2 + g], D2, D3);
   };
-  // the wave's run of tiles is walked row by row: (it, jt) advance together
-  // with t, so no tile index is divided out
-  int it = t0 / njt, jt = t0 - (t0 / njt) * njt;
-  int cur = -1;
-  if (NBS > 0 && t0 < t1) fetch_b(jt);
-  for (int t = t0; t < t1; ++t) {
-    const int g1 = it * 16 + l16, g2 = jt * 16 + l16;  // this lane's A row and B column
-    const bool ok1 = g1 < n1, ok2 = g2 < n2;
-    int in = it, jn = jt + 1;
-    if (jn == njt) {
-      jn = 0;
-      ++in;
-    }
-    mf64x4 cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
-    if (NBS > 0) {
-      if (it != cur) {
-        const cd* a1 = u1k + (ok1 ? g1 : 0);
-#pragma unroll
-        for (int s = 0; s < NR; ++s) {
-          const int nu = 4 * s + kq;
-          const cd a = a1[(long)(nu < nbnd ? nu : 0) * npwx1];
-          arc[s] = nu < nbnd ? f * a.x : 0.0;
-          aic[s] = nu < nbnd ? -f * a.y : 0.0;  // f conj(u1); rows past the sphere are never binned
-          naic[s] = -aic[s];
+  for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) bre[e] = bim[e] = 0.0;
+  // this workgroup's share of the nk nrun units (a k's tiles in nrun runs)
+  const long nunit = (long)nk * nrun;
+  int u = (int)(nunit * blockIdx.x / gridDim.x);
+  const int uend = (int)(nunit * (blockIdx.x + 1) / gridDim.x);
+  tables(u / nrun, 0);
+  __syncthreads();
+  const int l16 = lane & 15, kq = lane >> 4;
+  int which = 0;
+  for (; u < uend; ++u) {
+    const int k = u / nrun;
+    const int* o1 = o1s + which * (npwx1 + npwx2);
+    const int* o2 = o1 + npwx1;
+    const int n1 = npw1[k], n2 = npw2[k];
+    const double f = 4.0 * wk[k];
+    const int base = ((org[3 * k] + x0) * D2 + org[3 * k + 1]) * D3 + org[3 * k + 2];
+    const int nit = (n1 + 15) / 16, njt = (n2 + 15) / 16, ntile = nit * njt;
+    // this wave's tiles, among the waves of all the k's runs
+    const int piece = (u - k * nrun) * kRhoWaves + wave, npiece = kRhoWaves * nrun;
+    const int t0 = (int)((long)ntile * piece / npiece), t1 = (int)((long)ntile * (piece + 1) / npiece);
+    const cd* u1k = u1 + (long)k * nbnd * npwx1;
+    const cd* u2k = u2 + (long)k * nbnd * npwx2;
+    constexpr int NR = NBS > 0 ? NBS : 1;
+    // with the A entries in registers the weight f is folded into them
+    const double fb = NBS > 0 ? 1.0 : f;
+    double arc[NR], aic[NR], naic[NR], brc[NR], bic[NR];
+    int o1v[4];
+    // B entries of tile column jt (register path): unconditional loads from
+    // clamped addresses; a band past nbnd meets a zeroed A entry, and a column
+    // past the sphere is never binned
+    auto fetch_b = [&](int jt) {
+      const int g2 = jt * 16 + l16;
+      const cd* b2 = u2k + (g2 < n2 ? g2 : 0);
+  #pragma unroll
+      for (int s = 0; s < NR; ++s) {
+        const int nu = 4 * s + kq;
+        const cd b = b2[(long)(nu < nbnd ? nu : 0) * npwx2];
+        brc[s] = b.x;
+        bic[s] = b.y;
+      }
+    };
+    // the wave's run of tiles is walked row by row: (it, jt) advance together
+    // with t, so no tile index is divided out
+    int it = t0 / njt, jt = t0 - (t0 / njt) * njt;
+    int cur = -1;
+    if (NBS > 0 && t0 < t1) fetch_b(jt);
+    // the next k's tables under this k's tiles
+    const bool turn = u + 1 < uend && (u + 1) / nrun != k;
+    if (turn) tables(k + 1, which ^ 1);
+    for (int t = t0; t < t1; ++t) {
+      const int g1 = it * 16 + l16, g2 = jt * 16 + l16;  // this lane's A row and B column
+      const bool ok1 = g1 < n1, ok2 = g2 < n2;
+      int in = it, jn = jt + 1;
+      if (jn == njt) {
+        jn = 0;
+        ++in;
+      }
+      mf64x4 cr = {0.0, 0.0, 0.0, 0.0}, ci = {0.0, 0.0, 0.0, 0.0};
+      if (NBS > 0) {
+        if (it != cur) {
+          const cd* a1 = u1k + (ok1 ? g1 : 0);
+  #pragma unroll
+          for (int s = 0; s < NR; ++s) {
+            const int nu = 4 * s + kq;
+            const cd a = a1[(long)(nu < nbnd ? nu : 0) * npwx1];
+            arc[s] = nu < nbnd ? f * a.x : 0.0;
+            aic[s] = nu < nbnd ? -f * a.y : 0.0;  // f conj(u1); rows past the sphere are never binned
+            naic[s] = -aic[s];
+          }
+          // box offsets of this row's G1 (rows past the sphere get a bin
+          // outside the box)
+  #pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int gr = it * 16 + 4 * r + kq;
+            o1v[r] = gr < n1 ? o1[gr] : INT_MIN / 2;
+          }
+          cur = it;
         }
-        // box offsets of this row's G1 (rows past the sphere get a bin
-        // outside the box)
-#pragma unroll
+  #pragma unroll
+        for (int s = 0; s < NR; ++s) {
+          cr = mfma_16x16x4(arc[s], brc[s], cr);
+          cr = mfma_16x16x4(naic[s], bic[s], cr);
+          ci = mfma_16x16x4(arc[s], bic[s], ci);
+          ci = mfma_16x16x4(aic[s], brc[s], ci);
+        }
+        // the next tile's B loads run under this tile's binning
+        if (t + 1 < t1) fetch_b(jn);
+      } else {
+        const cd* a1 = u1k + (ok1 ? g1 : 0);
+        const cd* b2 = u2k + (ok2 ? g2 : 0);
+        for (int b0 = 0; b0 < nbnd; b0 += 4) {
+          const int nu = b0 + kq;
+          cd a = {0.0, 0.0}, b = {0.0, 0.0};
+          if (nu < nbnd) {
+            if (ok1) a = a1[(long)nu * npwx1];
+            if (ok2) b = b2[(long)nu * npwx2];
+          }
+          const double ar = a.x, ai = -a.y;  // conj(u1)
+          cr = mfma_16x16x4(ar, b.x, cr);
+          cr = mfma_16x16x4(-ai, b.y, cr);
+          ci = mfma_16x16x4(ar, b.y, ci);
+          ci = mfma_16x16x4(ai, b.x, ci);
+        }
+  #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int gr = it * 16 + 4 * r + kq;
-          o1v[r] = gr < n1 ? o1s[gr] : INT_MIN / 2;
+          o1v[r] = gr < n1 ? o1[gr] : INT_MIN / 2;
         }
-        cur = it;
       }
-#pragma unroll
-      for (int s = 0; s < NR; ++s) {
-        cr = mfma_16x16x4(arc[s], brc[s], cr);
-        cr = mfma_16x16x4(naic[s], bic[s], cr);
-        ci = mfma_16x16x4(arc[s], bic[s], ci);
-        ci = mfma_16x16x4(aic[s], brc[s], ci);
-      }
-      // the next tile's B loads run under this tile's binning
-      if (t + 1 < t1) fetch_b(jn);
-    } else {
-      const cd* a1 = u1k + (ok1 ? g1 : 0);
-      const cd* b2 = u2k + (ok2 ? g2 : 0);
-      for (int b0 = 0; b0 < nbnd; b0 += 4) {
-        const int nu = b0 + kq;
-        cd a = {0.0, 0.0}, b = {0.0, 0.0};
-        if (nu < nbnd) {
-          if (ok1) a = a1[(long)nu * npwx1];
-          if (ok2) b = b2[(long)nu * npwx2];
+      // this lane's results: G1 rows 4 r + kq of the tile, G2 column l16
+      if (ok2) {
+        const int c2 = o2[g2] - base;
+  #pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int bin = c2 - o1v[r];
+          // past the sphere, or another x-slice of the box
+          if ((unsigned)bin < (unsigned)nbin) {
+            atomicAdd(&bre[bin], fb * cr[r]);
+            atomicAdd(&bim[bin], fb * ci[r]);
+          }
         }
-        const double ar = a.x, ai = -a.y;  // conj(u1)
-        cr = mfma_16x16x4(ar, b.x, cr);
-        cr = mfma_16x16x4(-ai, b.y, cr);
-        ci = mfma_16x16x4(ar, b.y, ci);
-        ci = mfma_16x16x4(ai, b.x, ci);
       }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int gr = it * 16 + 4 * r + kq;
-        o1v[r] = gr < n1 ? o1s[gr] : INT_MIN / 2;
-      }
+      it = in;
+      jt = jn;
     }
-    // this lane's results: G1 rows 4 r + kq of the tile, G2 column l16
-    if (ok2) {
-      const int c2 = o2s[g2] - base;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int bin = c2 - o1v[r];
-        // past the sphere, or another x-slice of the box
-        if ((unsigned)bin < (unsigned)nbin) {
-          atomicAdd(&bre[bin], fb * cr[r]);
-          atomicAdd(&bim[bin], fb * ci[r]);
-        }
-      }
+    if (turn) {
+      __syncthreads();  // the other tables are whole, these are free
+      which ^= 1;
     }
-    it = in;
-    jt = jn;
   }
   __syncthreads();
-  cd* dst = part + ((long)k * D1 + x0) * D2 * D3;
+  cd* dst = part + ((long)blockIdx.x * D1 + x0) * D2 * D3;
   for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) dst[e] = {bre[e], bim[e]};
 }
 
@@ -432,7 +458,7 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
 // bins b with (org_k + b) = l (mod N) on every axis; then F = sum_c F_c in a
 // fixed order (no atomics in this reduction)
 __global__ __launch_bounds__(256) void drho_reduce_kernel(const cd* __restrict__ part, const int* __restrict__ org,
-                                                          int nk, int nchunk, int D1, int D2, int D3, int n1, int n2,
+                                                          int npart, int nk, int nchunk, int D1, int D2, int D3, int n1, int n2,
                                                           int n3, cd* __restrict__ Fc) {
   const long total = (long)n1 * n2 * n3;
   const long e = (long)blockIdx.x * 256 + threadIdx.x;
@@ -440,8 +466,9 @@ __global__ __launch_bounds__(256) void drho_reduce_kernel(const cd* __restrict__
   const int c = blockIdx.y;
   const int l3 = (int)(e % n3), l2 = (int)((e / n3) % n2), l1 = (int)(e / ((long)n2 * n3));
   double sr = 0.0, si = 0.0;
-  for (int k = c; k < nk; k += nchunk) {
-    const cd* pk = part + (long)k * D1 * D2 * D3;
+  for (int p = c; p < npart; p += nchunk) {
+    const cd* pk = part + (long)p * D1 * D2 * D3;
+    const int k = (int)((long)p * nk / npart);  // a k-point of the part
     for (int b1 = wrap(l1 - org[3 * k], n1); b1 < D1; b1 += n1)
       for (int b2 = wrap(l2 - org[3 * k + 1], n2); b2 < D2; b2 += n2)
         for (int b3 = wrap(l3 - org[3 * k + 2], n3); b3 < D3; b3 += n3) {
@@ -597,30 +624,56 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
   const int nk = ckq->nk;
   const int n1 = ckq->fft[0], n2 = ckq->fft[1], n3 = ckq->fft[2];
   const long nr = (long)n1 * n2 * n3;
-  // per-k origin of the Miller difference m(k+q) - m(k) and the common box
-  // (from each sphere's Miller bounds, kept by pw_set_kpoints)
+  // per-k origin of the Miller difference m(k+q) - m(k) and the size that holds
+  // every k's box from its own origin (D) or all k from one origin (DA); from
+  // each sphere's Miller bounds, kept by pw_set_kpoints
   std::vector<int> org(3 * (size_t)nk);
-  int D[3] = {1, 1, 1};
-  for (int k = 0; k < nk; ++k) {
+  int D[3] = {1, 1, 1}, lo[3], DA[3];
+  for (int a = 0; a < 3; ++a) {
+    int dlo = 1 << 20, dhi = -(1 << 20);
+    for (int k = 0; k < nk; ++k) {
+      const int l = ckq->mlo[3 * k + a] - ck->mhi[3 * k + a], h = ckq->mhi[3 * k + a] - ck->mlo[3 * k + a];
+      org[3 * k + a] = l;
+      D[a] = std::max(D[a], h - l + 1);
+      dlo = std::min(dlo, l);
+      dhi = std::max(dhi, h);
+    }
+    lo[a] = dlo;
+    DA[a] = std::max(1, dhi - dlo + 1);
+  }
+  // LDS: bins of a slice of the box, then the tables of both spheres' offsets
+  // (x-layers of box d in one slice, 0 if not one fits)
+  const size_t table = sizeof(int) * (size_t)(ck->npwx + ckq->npwx);
+  auto slice = [&](const int* d, int ntab, size_t lds) -> long {
+    const size_t per_x = 2 * sizeof(double) * (size_t)d[1] * d[2], rest = ntab * table + 16 + 2 * sizeof(double);
+    return rest < lds ? (long)std::min<size_t>(d[0], (lds - rest) / per_x) : 0;
+  };
+  long nx = slice(D, 1, 150 * 1024);
+  if (nx < 1) return set_err(ckq, PW_EINVAL, "drho: plane-wave spheres too large for the bins");
+  // One origin for all k, so that a workgroup bins runs of several k into one
+  // box, unless that box takes more slices than a box per k (k-points far
+  // apart in Miller space): the pair products are formed once per slice
+  const long na = slice(DA, 2, 160 * 1024);
+  const bool one = na > 0 && (DA[0] + na - 1) / na <= (D[0] + nx - 1) / nx;
+  if (one) {
+    nx = na;
     for (int a = 0; a < 3; ++a) {
-      const int lo1 = ck->mlo[3 * k + a], hi1 = ck->mhi[3 * k + a];
-      const int lo2 = ckq->mlo[3 * k + a], hi2 = ckq->mhi[3 * k + a];
-      org[3 * k + a] = lo2 - hi1;
-      D[a] = std::max(D[a], hi2 - lo1 - (lo2 - hi1) + 1);
+      D[a] = DA[a];
+      for (int k = 0; k < nk; ++k) org[3 * k + a] = lo[a];
     }
   }
-  // LDS: bins of a slice of the box, then the Miller keys of both spheres
-  const size_t tiles = sizeof(int) * (size_t)(ck->npwx + ckq->npwx) + 16;
-  const size_t lds_max = 150 * 1024;
-  const size_t per_x = 2 * sizeof(double) * (size_t)D[1] * D[2];
-  if (per_x + tiles + 2 * sizeof(double) > lds_max) return set_err(ckq, PW_EINVAL, "drho: plane-wave spheres too large for the bins");
-  const int nx = (int)std::min<size_t>(D[0], (lds_max - tiles - 2 * sizeof(double)) / per_x);
+  // runs per k: some four for each CU, so that uneven shares differ little,
+  // but two tiles or more per wave; with a box per k one for each CU
+  const int ntile = ((ck->npwmax + 15) / 16) * ((ckq->npwmax + 15) / 16);
+  const int nrun = std::max(1, std::min(one ? (4 * kDrhoWgs + nk - 1) / nk : kDrhoWgs / nk, ntile / (2 * kRhoWaves)));
+  const int npart = one ? (int)std::min<long>((long)nk * nrun, kDrhoWgs) : nk * nrun;
+  const size_t per_x = 2 * sizeof(double) * (size_t)D[1] * D[2], tiles = (one ? 2 : 1) * table + 16;
   DevBufs b(ckq);
   cd *part, *F, *tmp, *Fc;
   int* d_org;
   double* d_w;
-  const int nchunk = std::min(nk, 64);
-  MKPW_TRY(b.get((size_t)nk * D[0] * D[1] * D[2], &part));
+  const int nchunk = std::min((npart + 7) / 8, 64);
+  MKPW_TRY(b.get((size_t)npart * D[0] * D[1] * D[2], &part));
   MKPW_TRY(b.get((size_t)nchunk * nr, &Fc));
   MKPW_TRY(b.get((size_t)nr, &F));
   MKPW_TRY(b.get((size_t)nr, &tmp));
@@ -633,14 +686,14 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
   const int nbs = nbnd <= 8 ? 2 : nbnd <= 16 ? 4 : 0;  // band steps held in registers
   const void* kern = nbs == 2 ? (const void*)drho_mfma_kernel<2>
                      : nbs == 4 ? (const void*)drho_mfma_kernel<4> : (const void*)drho_mfma_kernel<0>;
-  for (int x0 = 0; x0 < D[0]; x0 += nx) {
-    const int nxx = std::min(nx, D[0] - x0);
+  for (int x0 = 0; x0 < D[0]; x0 += (int)nx) {
+    const int nxx = std::min((int)nx, D[0] - x0);
     const size_t lds = per_x * nxx + tiles + 2 * sizeof(double);
     MKPW_TRY(ensure_lds_limit(ckq, kern, lds));
-#define MKPW_DRHO(NBS)                                                                                             \
-  hipLaunchKernelGGL(drho_mfma_kernel<NBS>, dim3((unsigned)nk), dim3(kRhoWaves * 64), lds, st, nbnd, d_w, ck->d_npw, \
-                     ck->d_mkey, ck->npwx, (const cd*)psi_k, ckq->d_npw, ckq->d_mkey, ckq->npwx, (const cd*)dpsi_kq,  \
-                     d_org, D[0], D[1], D[2], x0, nxx, part)
+#define MKPW_DRHO(NBS)                                                                                              \
+  hipLaunchKernelGGL(drho_mfma_kernel<NBS>, dim3((unsigned)npart), dim3(kRhoWaves * 64), lds, st, nk, nrun, \
+                     nbnd, d_w, ck->d_npw, ck->d_mkey, ck->npwx, (const cd*)psi_k, ckq->d_npw, ckq->d_mkey,         \
+                     ckq->npwx, (const cd*)dpsi_kq, d_org, D[0], D[1], D[2], x0, nxx, part)
     if (nbs == 2) MKPW_DRHO(2);
     else if (nbs == 4) MKPW_DRHO(4);
     else MKPW_DRHO(0);
@@ -648,8 +701,8 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
     MKPW_TRY(check_launch(ckq, "drho_pairs", st));
   }
   const dim3 grid((unsigned)((nr + 255) / 256));
-  hipLaunchKernelGGL(drho_reduce_kernel, dim3(grid.x, (unsigned)nchunk), dim3(256), 0, st, part, d_org, nk, nchunk,
-                     D[0], D[1], D[2], n1, n2, n3, Fc);
+  hipLaunchKernelGGL(drho_reduce_kernel, dim3(grid.x, (unsigned)nchunk), dim3(256), 0, st, part, d_org, npart, nk,
+                     nchunk, D[0], D[1], D[2], n1, n2, n3, Fc);
   hipLaunchKernelGGL(sum_chunks_kernel, grid, dim3(256), 0, st, Fc, nchunk, nr, F);
   // drho(r) = sum_f F(f) exp(+2 pi i f.l / N)
   hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, F, tmp, n1, n2, n3, 0, 1, 1.0);
