@@ -19,8 +19,8 @@
 //      solve shrinks the components along the other eigenvectors by their
 //      gap over that error), then Gram-Schmidt (twice) within each cluster of
 //      eigenvalues closer than 1e-3 of the matrix norm;
-//   5. back through D and the reflectors: x = H_0 (... H_{n-3} (D y)), four
-//      eigenvectors per wave at once.
+//   5. back through D and the reflectors: x = H_0 (... H_{n-3} (D y)), sixteen
+//      lanes per eigenvector.
 // About (4/3) n^3 complex multiply-adds, against roughly 30 n^3 for the cyclic
 // Jacobi sweeps this replaces.
 //
@@ -44,7 +44,6 @@ constexpr int kEigLd = kEigMax + 1;
 constexpr int kEigYs = kEigMax + 1;
 constexpr int kEigNev = 32;   // most eigenpairs returned
 constexpr int kEigThreads = 512;             // one workgroup per k-point
-constexpr int kEigWaves = kEigThreads / 64;
 constexpr int kEigPQ = 8;                    // work-items per row of the reduction (one DPP group)
 static_assert(kEigPQ * kEigMax <= kEigThreads, "one row of the trailing block per group of kEigPQ");
 
@@ -481,42 +480,73 @@ __global__ __launch_bounds__(kEigThreads) void heevx_kernel(const cd* __restrict
   }
   __syncthreads();
 
-  // ---- 5. x = H_0 (... H_{n-3} (D y)): wave v takes eigenpairs v, v + 8, ...
-  //         (at most four), all of them together so that their lane sums are
-  //         independent and overlap; lane i holds component i
+  // ---- 5. x = H_0 (... H_{n-3} (D y)): sixteen lanes per eigenpair, lane q its
+  //         components q + 16 s in registers, so that a reflector takes one sum
+  //         over a row of 16 lanes per eigenpair (a whole wave per eigenpair
+  //         spent its issue slots on the lane sums: 143e3 of the 600e3 cycles
+  //         of a 62 x 62 problem with 20 eigenpairs, 64e3 now)
   {
-    constexpr int kPerWave = kEigNev / kEigWaves;
-    cd zi[kPerWave];
+    constexpr int kC = kEigMax / 16;
+    static_assert(kEigNev * 16 <= kEigThreads, "sixteen work-items per eigenpair");
+    const int t = tid >> 4, q = tid & 15;
+    cd z[kC], u[kC], un[kC];
 #pragma unroll
-    for (int s2 = 0; s2 < kPerWave; ++s2) {
-      const int t = wave + kEigWaves * s2;
-      const double yv = (t < nev && lane < n) ? Yr[t * kEigYs + lane] : 0.0;
-      zi[s2] = lane < n ? cd{S.ph[lane].x * yv, S.ph[lane].y * yv} : cd{0.0, 0.0};
+    for (int c = 0; c < kC; ++c) {
+      const int i = q + 16 * c;
+      const double yv = t < nev && i < n ? Yr[t * kEigYs + i] : 0.0;
+      z[c] = i < n ? cd{S.ph[i].x * yv, S.ph[i].y * yv} : cd{0.0, 0.0};
     }
-    __syncthreads();  // Z overwrites Y: every wave has its rows in registers first
-    for (int j = n - 3; j >= 0; --j) {
-      const double gj = S.g[j];
-      if (gj == 0.0) continue;
-      cd u = {0.0, 0.0};
-      if (lane > j && lane < n) u = A[pk(lane, j)];
-      double cr[kPerWave], ci[kPerWave];
+    __syncthreads();  // Z overwrites Y: every row is in registers first
+    if (4 * wave < nev) {
+      auto load_u = [&](int j, cd(&x)[kC]) {
 #pragma unroll
-      for (int s2 = 0; s2 < kPerWave; ++s2) {
-        // c = g u^H z
-        cr[s2] = wave_sum64(u.x * zi[s2].x + u.y * zi[s2].y);
-        ci[s2] = wave_sum64(u.x * zi[s2].y - u.y * zi[s2].x);
+        for (int c = 0; c < kC; ++c) {
+          const int i = q + 16 * c;
+          const bool ok = i > j && i < n;
+          x[c] = A[ok ? pk(i, j) : 0];
+          if (!ok) x[c] = {0.0, 0.0};
+        }
+      };
+      double gj = 0.0;
+      if (n >= 3) {
+        load_u(n - 3, u);
+        gj = S.g[n - 3];
       }
+      for (int j = n - 3; j >= 0; --j) {
+        const double gn = S.g[j > 0 ? j - 1 : 0];
+        load_u(j > 0 ? j - 1 : 0, un);
+        // z -= u (g u^H z), two partial sums to each of Re and Im
+        double cr[2], ci[2];
 #pragma unroll
-      for (int s2 = 0; s2 < kPerWave; ++s2) {
-        const double a = gj * cr[s2], b = gj * ci[s2];
-        zi[s2].x -= a * u.x - b * u.y;
-        zi[s2].y -= a * u.y + b * u.x;
+        for (int c = 0; c < kC; ++c) {
+          const double r = u[c].x * z[c].x + u[c].y * z[c].y, i = u[c].x * z[c].y - u[c].y * z[c].x;
+          cr[c & 1] = c < 2 ? r : cr[c & 1] + r;
+          ci[c & 1] = c < 2 ? i : ci[c & 1] + i;
+        }
+        double a = cr[0] + cr[1], b = ci[0] + ci[1];
+        a += dpp<0xB1>(a);
+        b += dpp<0xB1>(b);
+        a += dpp<0x4E>(a);
+        b += dpp<0x4E>(b);
+        a += dpp<0x141>(a);
+        b += dpp<0x141>(b);
+        a += dpp<0x140>(a);
+        b += dpp<0x140>(b);
+        a *= gj;
+        b *= gj;
+#pragma unroll
+        for (int c = 0; c < kC; ++c) {
+          z[c].x -= a * u[c].x - b * u[c].y;
+          z[c].y -= a * u[c].y + b * u[c].x;
+          u[c] = un[c];
+        }
+        gj = gn;
       }
-    }
+      if (t < nev) {
 #pragma unroll
-    for (int s2 = 0; s2 < kPerWave; ++s2) {
-      const int t = wave + kEigWaves * s2;
-      if (t < nev && lane < n) Zr[t * kEigLd + lane] = zi[s2];
+        for (int c = 0; c < kC; ++c)
+          if (q + 16 * c < n) Zr[t * kEigLd + q + 16 * c] = z[c];
+      }
     }
   }
   __syncthreads();
