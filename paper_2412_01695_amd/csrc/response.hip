@@ -279,6 +279,184 @@ __global__ __launch_bounds__(kDvWaves * 64) void dvpsi_mfma_kernel(
   }
 }
 
+// The same product where the box fits in LDS: one workgroup of eight waves per
+// CU stages the box once and takes its (k, band group, run of row tiles) units
+// in turn, each wave up to dvl_tiles(NG) tiles that share the B values.  psi is
+// staged in Miller order through the permutation (one value per work-item, the
+// next block's on its way under this block's products); blocks past the sphere
+// hold zeros, and the column offsets there repeat the last one's.  The tables of
+// the next unit are filled under this unit's products.  2048 k x 8 bands
+// [314 x 314], box 19^3: 297 us; 322 us with the box read from L2, and 37 us
+// for a pass that put psi in Miller order.  The matrix cores are busy 58% of
+// the time at the clock they run at under this load; blocks twice as long and
+// reads issued two steps ahead changed nothing, tiles in turn instead of
+// interleaved took 315 us.
+constexpr int kDlWaves = 8;
+__host__ __device__ constexpr int dvl_tiles(int ng) { return ng == 1 ? 3 : 2; }  // of a wave, what its registers hold
+__host__ __device__ constexpr int dvl_steps(int ng) { return ng == 1 ? 4 : 2; }  // of four plane waves, issued together
+__host__ __device__ constexpr size_t dvl_lds_bytes(long nbox, int ng, int kc, int npwx_in) {
+  return sizeof(cd) * ((size_t)nbox + 2 * (size_t)(8 * ng) * (kc + 1)) + 4 * sizeof(int) * (size_t)npwx_in;
+}
+
+template <int NG, int NT>
+__device__ __forceinline__ void dvl_block(const char* bx, const int* wc, int nch, const int (&prow)[dvl_tiles(NG)],
+                                          const double* const (&bl)[NG], int kq, mf64x4 (&d1)[dvl_tiles(NG)][NG],
+                                          mf64x4 (&d2)[dvl_tiles(NG)][NG]) {
+  typedef double lds2 __attribute__((ext_vector_type(2)));
+  constexpr int kU = dvl_steps(NG);
+  for (int c = 0; c < nch; ++c) {
+    double bv[kU][NG];
+    lds2 av[kU][NT];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int g = 4 * (c * kU + u) + kq;
+      const int w = wc[g];
+#pragma unroll
+      for (int j = 0; j < NG; ++j) bv[u][j] = bl[j][2 * g];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) av[u][i] = *reinterpret_cast<const lds2*>(bx + (prow[i] + w));
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+          d1[i][j] = mfma_16x16x4(av[u][i][0], bv[u][j], d1[i][j]);
+          d2[i][j] = mfma_16x16x4(av[u][i][1], bv[u][j], d2[i][j]);
+        }
+      }
+    }
+  }
+}
+
+template <int NG>
+__global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
+    const cd* __restrict__ box, int nbox, int s2, int s3, int lo1, int lo2, int lo3, int kcs,
+    const int* __restrict__ npw_in, const int* __restrict__ key_in, const int* __restrict__ perm_in, int npwx_in,
+    const cd* __restrict__ psi, const int* __restrict__ npw_out, const int* __restrict__ key_out,
+    const int* __restrict__ perm_out, int npwx_out, cd* __restrict__ out, int nk, int nbnd, int nsplit,
+    double scale) {
+  constexpr int NB = 8 * NG, kDlTiles = dvl_tiles(NG);
+  extern __shared__ __align__(16) char smem[];
+  const int KC = 1 << kcs, BS = KC + 1;
+  cd* Bs = reinterpret_cast<cd*>(smem) + nbox;           // [2][NB][BS]
+  int* wcol = reinterpret_cast<int*>(Bs + 2 * NB * BS);  // [npwx_in]: byte offset of -m_G
+  int* pin = wcol + 2 * npwx_in;                         // [npwx_in]: the k's Miller order; both twice
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kq = lane >> 4, part = l16 >> 3;
+  for (int e = tid; e < nbox; e += kDlWaves * 64) reinterpret_cast<cd*>(smem)[e] = box[e];
+  const int nbt = (nbnd + NB - 1) / NB;
+  const int rowoff = ((lo1 * s2) + lo2) * s3 + lo3;
+  const int sb = tid >> kcs, sg = tid & (KC - 1);  // the band and plane wave this work-item stages
+  const int nunit = nk * nbt * nsplit;
+  struct Unit {
+    int k, bt, sp, nin, nout, t0, nt;
+    const cd* src;  // the row this work-item stages, null if none
+    int prow[kDlTiles];
+  };
+  auto unit = [&](int un) {
+    Unit v;
+    v.k = un / (nbt * nsplit);
+    const int rest = un - v.k * nbt * nsplit;
+    v.bt = rest / nsplit;
+    v.sp = rest - v.bt * nsplit;
+    v.nin = npw_in[v.k];
+    v.nout = npw_out[v.k];
+    const int tiles = (v.nout + 15) / 16, per = (tiles + nsplit - 1) / nsplit;  // per <= kDlWaves kDlTiles
+    v.t0 = min(tiles, v.sp * per);
+    const int t1 = min(tiles, v.t0 + per);
+    v.nt = v.t0 + wave < t1 ? (t1 - v.t0 - wave + kDlWaves - 1) / kDlWaves : 0;  // of this wave
+    const int* key = key_out + (long)v.k * npwx_out;
+    const int* pk = perm_out + (long)v.k * npwx_out;
+#pragma unroll
+    for (int i = 0; i < kDlTiles; ++i) {
+      const int gp = (v.t0 + wave + kDlWaves * i) * 16 + l16;
+      v.prow[i] = i < v.nt ? 16 * (miller_lin(key[pk[min(gp, v.nout - 1)]], s2, s3) - rowoff) : 0;
+    }
+    const int band = v.bt * NB + sb;
+    v.src = sb < NB && band < nbnd ? psi + ((long)v.k * nbnd + band) * npwx_in : nullptr;
+    return v;
+  };
+  auto tables = [&](const Unit& v, int which) {
+    for (int g = tid; g < npwx_in; g += kDlWaves * 64) {
+      const int p = v.nin > 0 ? perm_in[(long)v.k * npwx_in + min(g, v.nin - 1)] : 0;
+      pin[which * npwx_in + g] = p;
+      wcol[which * npwx_in + g] = v.nin > 0 ? -16 * miller_lin(key_in[(long)v.k * npwx_in + p], s2, s3) : 0;
+    }
+  };
+  auto fetch = [&](const Unit& v, int which, int b0) {
+    return v.src && b0 + sg < v.nin ? v.src[pin[which * npwx_in + b0 + sg]] : cd{0.0, 0.0};
+  };
+  int un = blockIdx.x, which = 0, buf = 0;  // gridDim.x <= nunit
+  Unit v = unit(un);
+  tables(v, 0);
+  __syncthreads();
+  cd next = fetch(v, 0, 0);
+  for (;;) {
+    const bool more = un + (int)gridDim.x < nunit;
+    Unit nv;
+    mf64x4 d1[kDlTiles][NG], d2[kDlTiles][NG];
+#pragma unroll
+    for (int i = 0; i < kDlTiles; ++i)
+#pragma unroll
+      for (int j = 0; j < NG; ++j) d1[i][j] = d2[i][j] = mf64x4{0.0, 0.0, 0.0, 0.0};
+    const int* wc = wcol + which * npwx_in;
+    for (int b0 = 0; b0 < v.nin; b0 += KC, buf ^= 1) {
+      cd* bb = Bs + buf * NB * BS;
+      if (sb < NB) bb[sb * BS + sg] = next;
+      __syncthreads();
+      if (b0 + KC < v.nin) next = fetch(v, which, b0 + KC);
+      if (b0 == 0 && more) {  // the next unit's tables, under this unit's products
+        nv = unit(un + gridDim.x);
+        tables(nv, which ^ 1);
+      }
+      const double* bl[NG];
+#pragma unroll
+      for (int j = 0; j < NG; ++j) bl[j] = reinterpret_cast<const double*>(bb + (j * 8 + (l16 & 7)) * BS) + part;
+      const int nch = (min(KC, v.nin - b0) + 4 * dvl_steps(NG) - 1) / (4 * dvl_steps(NG));
+      if (v.nt == kDlTiles) dvl_block<NG, kDlTiles>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+      else if (kDlTiles > 2 && v.nt == 2) dvl_block<NG, 2>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+      else if (v.nt == 1) dvl_block<NG, 1>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+    }
+    if (more) {
+      if (v.nin <= 0) {
+        nv = unit(un + gridDim.x);
+        tables(nv, which ^ 1);
+      }
+      __syncthreads();  // the next unit's tables are whole
+      next = fetch(nv, which ^ 1, 0);
+    }
+    // lane (kq, c), c < 8: D1 and D2 of band column c, its partner lane c + 8
+    // those of the imaginary column: Re = D1[c] - D2[c + 8], Im = D1[c + 8] + D2[c]
+    const int* pk = perm_out + (long)v.k * npwx_out;
+#pragma unroll
+    for (int i = 0; i < kDlTiles; ++i) {
+      if (i >= v.nt) break;
+#pragma unroll
+      for (int j = 0; j < NG; ++j) {
+        const int ob = v.bt * NB + j * 8 + (l16 & 7);
+        cd* orow = out + ((long)v.k * nbnd + (ob < nbnd ? ob : 0)) * npwx_out;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const double o1 = __shfl_xor(d1[i][j][r], 8, 64), o2 = __shfl_xor(d2[i][j][r], 8, 64);
+          const int gq = (v.t0 + wave + kDlWaves * i) * 16 + 4 * r + kq;
+          if (part == 0 && ob < nbnd && gq < v.nout)
+            orow[pk[gq]] = {scale * (d1[i][j][r] - o2), scale * (o1 + d2[i][j][r])};
+        }
+      }
+    }
+    // the padding of the k+q rows
+    if (v.sp == 0)
+      for (int b = v.bt * NB + wave; b < min(nbnd, v.bt * NB + NB); b += kDlWaves)
+        for (int g = v.nout + lane; g < npwx_out; g += 64) out[((long)v.k * nbnd + b) * npwx_out + g] = {0.0, 0.0};
+    if (!more) break;
+    v = nv;
+    un += gridDim.x;
+    which ^= 1;
+  }
+}
+
 constexpr int kRhoWaves = 16;  // waves per workgroup of drho_mfma_kernel
 constexpr int kDrhoWgs = 256;  // its workgroups that run at once, one per CU
 
@@ -556,16 +734,43 @@ extern "C" pw_status pw_dfpt_rhs(pw_ctx* ckq, const pw_ctx* ck, int nocc, const 
   MKPW_TRY(b.get((size_t)nk * nocc * nocc, &W));
   MKPW_TRY(transform_dv(ckq, (const double*)dv_r, dvt, tmp, st));
   // rhs0 = -dV u (on the k+q sphere)
-  const int ng = nocc <= 8 ? 1 : nocc <= 16 ? 2 : 4;  // groups of 8 bands per wave
-  {
-    // the box of differences for all k, and psi_k with each sphere in Miller
-    // order (with the k+q rows also taken in Miller order, the 64 L entries of
-    // one step are a few runs of neighbours in the box)
-    cd *box, *psi_sorted;
-    MKPW_TRY(b.get((size_t)nbox, &box));
+  // the box of differences for all k
+  cd* box;
+  MKPW_TRY(b.get((size_t)nbox, &box));
+  hipLaunchKernelGGL(dv_box_kernel, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st, dvt, ckq->fft[0],
+                     ckq->fft[1], ckq->fft[2], lo[0], lo[1], lo[2], sz[0], sz[1], sz[2], box);
+  // in LDS where it fits beside a block of psi
+  const int gl = nocc <= 8 ? 1 : 2;
+  const size_t room = 160 * 1024;
+  int kcs = gl == 1 ? 6 : 5;  // 64 / gl plane waves a block, or half as many
+  const bool in_lds = nbox <= (long)(room / sizeof(cd)) &&
+                      (dvl_lds_bytes(nbox, gl, 1 << kcs, ck->npwx) <= room ||
+                       dvl_lds_bytes(nbox, gl, 1 << --kcs, ck->npwx) <= room);
+  if (in_lds) {
+    const int tiles = (ckq->npwmax + 15) / 16, nbt = (nocc + 8 * gl - 1) / (8 * gl);
+    // few k: as many runs of row tiles as give every CU a workgroup, at least
+    // a tile per wave
+    const int most = (tiles + kDlWaves - 1) / kDlWaves, least = (tiles + kDlWaves * dvl_tiles(gl) - 1) / (kDlWaves * dvl_tiles(gl));
+    const int nsplit = std::max(std::max(1, least), std::min(most, 256 / std::max(1, nk * nbt)));
+    const size_t lds = dvl_lds_bytes(nbox, gl, 1 << kcs, ck->npwx);
+    const void* kern = gl == 1 ? (const void*)dvpsi_lds_kernel<1> : (const void*)dvpsi_lds_kernel<2>;
+    MKPW_TRY(ensure_lds_limit(ckq, kern, lds));
+    const unsigned wgs = (unsigned)std::min<long>((long)nk * nbt * nsplit, 256);
+#define MKPW_DVL(NG)                                                                                                 \
+  hipLaunchKernelGGL(dvpsi_lds_kernel<NG>, dim3(wgs), dim3(kDlWaves * 64), lds, st, box, (int)nbox, sz[1], sz[2], lo[0], \
+                     lo[1], lo[2], kcs, ck->d_npw, ck->d_mkey, ck->d_lexperm, ck->npwx, (const cd*)psi_k, ckq->d_npw, \
+                     ckq->d_mkey, ckq->d_lexperm, ckq->npwx, (cd*)rhs, nk, nocc, nsplit, -1.0)
+    if (gl == 1) MKPW_DVL(1);
+    else MKPW_DVL(2);
+#undef MKPW_DVL
+    MKPW_TRY(check_launch(ckq, "dvpsi", st));
+  } else {
+    // psi_k with each sphere in Miller order (with the k+q rows also taken in
+    // Miller order, the 64 L entries of one step are a few runs of neighbours
+    // in the box)
+    const int ng = nocc <= 8 ? 1 : nocc <= 16 ? 2 : 4;  // groups of 8 bands per wave
+    cd* psi_sorted;
     MKPW_TRY(b.get((size_t)nk * nocc * ck->npwx, &psi_sorted));
-    hipLaunchKernelGGL(dv_box_kernel, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st, dvt, ckq->fft[0],
-                       ckq->fft[1], ckq->fft[2], lo[0], lo[1], lo[2], sz[0], sz[1], sz[2], box);
     hipLaunchKernelGGL(permute_rows_kernel,
                        dim3((unsigned)std::min<long>(64, ((long)nocc * ck->npwx + 255) / 256), (unsigned)nk),
                        dim3(256), 0, st, (const cd*)psi_k, ck->d_lexperm, ck->d_npw, ck->npwx, nocc, psi_sorted);
