@@ -868,9 +868,10 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
     }
   }
   // runs per k: some four for each CU, so that uneven shares differ little,
-  // but two tiles or more per wave; with a box per k one for each CU
+  // but eight tiles or more per wave (each workgroup writes a box, which the sum
+  // over boxes reads again); with a box per k one for each CU
   const int ntile = ((ck->npwmax + 15) / 16) * ((ckq->npwmax + 15) / 16);
-  const int nrun = std::max(1, std::min(one ? (4 * kDrhoWgs + nk - 1) / nk : kDrhoWgs / nk, ntile / (2 * kRhoWaves)));
+  const int nrun = std::max(1, std::min(one ? (4 * kDrhoWgs + nk - 1) / nk : kDrhoWgs / nk, ntile / (8 * kRhoWaves)));
   const int npart = one ? (int)std::min<long>((long)nk * nrun, kDrhoWgs) : nk * nrun;
   const size_t per_x = 2 * sizeof(double) * (size_t)D[1] * D[2], tiles = (one ? 2 : 1) * table + 16;
   DevBufs b(ckq);
