@@ -498,6 +498,16 @@ def serving_sample(n, rate=20.0, timeout_s=900):
     return json.loads(lines[-1])
 
 
+def kernel_flops(variant, cfg, npw, flops_kb):
+    """(kernel, flops per k-band) of the kernel that ran: variant 6 is the dense
+    product (8 npw^2 for the local term, 16 npw nproj for the projectors),
+    otherwise the pruned transforms' count `flops_kb`."""
+    if variant != 6:
+        return "hpsi_kernel", flops_kb
+    n = np.asarray(npw, float)
+    return "hpsi_dense_kernel", float(np.mean(8.0 * n * n + 16.0 * n * cfg.nproj))
+
+
 def hpsi_sample(torch, mkpw, cid, steps, warmup):
     """FP64 and mixed H|psi> throughput of another whole workload, with the
     roofline fractions of its autotuned kernels."""
@@ -519,8 +529,10 @@ def hpsi_sample(torch, mkpw, cid, steps, warmup):
         for name, prec, psi, h, peak in (("fp64", mkpw.PW_FP64, psi64, h64, PEAK_FP64_TFLOPS),
                                          ("mixed", mkpw.PW_MIXED, psi32, h32, PEAK_FP32_TFLOPS)):
             ms, _ = time_hpsi(torch, mkpw, s.ctx, prec, cfg.nbnd, psi, h, steps, warmup)
-            tf = flops_kb * nkb / (ms * 1e-3) / 1e12
+            kern, kern_flops = kernel_flops(mkpw.pw_get_option(s.ctx, "hpsi_variant_tuned"), cfg, s.npw, flops_kb)
+            tf = kern_flops * nkb / (ms * 1e-3) / 1e12
             out[name] = {"ms_per_call": ms, "kband_per_s": nkb / (ms * 1e-3), "tflops": tf, "roofline_frac": tf / peak,
+                         "kernel": kern, "kernel_flops_per_kband": kern_flops,
                          "shape": {k: mkpw.pw_get_option(s.ctx, f"hpsi_{k}_tuned")
                                    for k in ("variant", "slab", "threads")}}
         return cfg.name, out
@@ -629,7 +641,8 @@ def main():
     io_kb = io64_kb if key == "fp64" else io32_kb
     io_3p = io64_3p if key == "fp64" else io32_3p
     value = nkb / (ms * 1e-3)
-    flops_launch = flops_kb * nkb
+    kern, kern_flops = kernel_flops(shapes[key]["variant"], cfg, sysm.npw, flops_kb)
+    flops_launch = kern_flops * nkb
     achieved_tf = flops_launch / (ms * 1e-3) / 1e12
     res = {
         "metric": "k-band H|psi>/s (FP64 vs mixed FP32) at 1e-6 Ry; p50/p99 solve latency",
@@ -655,7 +668,7 @@ def main():
                      "frac": achieved_tf / (PEAK_FP64_TFLOPS if key == "fp64" else PEAK_FP32_TFLOPS),
                      "traffic": measured_traffic(cfg.name, key, shapes[key]),
                      "traffic_unit": "HBM bytes per launch (counters; null if not taken on this kernel)",
-                     "kernel": "hpsi_kernel", "shape": shapes[key], "flops_per_kband": flops_kb,
+                     "kernel": kern, "shape": shapes[key], "flops_per_kband": kern_flops,
                      "io_bytes_per_launch": io_kb * nkb,
                      "hbm_io_GBs": io_kb * nkb / (ms * 1e-3) / 1e9,
                      "hbm_frac": io_kb * nkb / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
@@ -666,7 +679,8 @@ def main():
         res["mixed"] = {"value": nkb / (out["mixed"] * 1e-3), "ms_per_step": out["mixed"], "dtype": "c64",
                         "shape": shapes["mixed"],
                         "speedup_vs_fp64": out["fp64"] / out["mixed"],
-                        "roofline_frac": flops_launch / (out["mixed"] * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
+                        "roofline_frac": kernel_flops(shapes["mixed"]["variant"], cfg, sysm.npw, flops_kb)[1]
+                        * nkb / (out["mixed"] * 1e-3) / 1e12 / PEAK_FP32_TFLOPS,
                         "traffic": measured_traffic(cfg.name, "mixed", shapes["mixed"]),
                         "io_bytes_per_launch": io32_kb * nkb}
     eigs = {}
