@@ -873,18 +873,38 @@ pw_status launch_one(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, 
   // small launches, and launches that may not allocate (the tuning times
   // candidates with events and builds their potentials), take a fixed shape
   if ((long)t.nk * sel.nvec < kTuneMinRows || vscratch) {
-    // (x lines as convolutions with one work-item per line; over 2 to 64 k x 8 to
-    // 24 vectors within 5% of the best of every shape on each mesh at 256
-    // work-items below 30^3 and 512 from there; 52 Ry at 30^3, 64 k x 24 vectors:
-    // 145 us against 210 for lane pairs, the best variant without the convolution
-    // 170)
+    // (x lines as convolutions with one work-item per line, 256 work-items below
+    // 30^3 and 512 from there: 18^3 FP64 560 k x 2 33 us against 38 without the
+    // convolution, 30^3 119 against 156.  Without it on 20^3 and 24^3, where the
+    // order is the other way round: 20^3 FP64 1000 k x 1 34 against 38, 24^3
+    // complex64 560 k x 2 36 against 42)
     HpsiShape sh;
-    sh.variant = WC < N ? 4 : (N % 2 == 0 && N >= 30) ? 2 : 1;
+    constexpr bool conv = WC < N && N != 20 && N != 24;
+    sh.variant = conv ? 4 : (N % 2 == 0 && N >= 30) ? 2 : 1;
     sh.threads = N >= 30 ? 512 : 256;
     const int lanes = sh.variant == 2 ? 2 : 1;
     if (!hpsi_kernel_ptr<T, N, WC>(sh)) sh.threads = 256;
-    sh.l3c = std::min(N, std::max(1, sh.threads / (lanes * N)));
-    while (sh.l3c > 1 && hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) > kLdsPerCu / 2) --sh.l3c;
+    const int lmax = std::min(N, std::max(1, sh.threads / (lanes * N)));
+    if (N < 30) {  // a slab that fills the work-items, two workgroups per CU
+      sh.l3c = lmax;
+      while (sh.l3c > 1 && hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) > kLdsPerCu / 2) --sh.l3c;
+    } else {
+      // each pass over a slab takes about one line's latency: the fewest passes
+      // per row and workgroup that a CU holds, the smaller slab of equals (two
+      // workgroups whatever the passes: 30^3 FP64 560 k x 2 230 us, 119 so)
+      const long held = std::min<long>(1024 / sh.threads, ((long)t.nk * sel.nvec + 255) / 256);
+      double least = 1e30;
+      sh.l3c = 1;
+      for (int l = 1; l <= lmax; ++l) {
+        const long lds = (long)hpsi_lds<T, N, WC>(t, l, nproj, sh.threads);
+        if (lds > (long)kLdsPerCu) break;
+        const double passes = (double)((N + l - 1) / l) / (double)std::max(1L, std::min(held, (long)kLdsPerCu / lds));
+        if (passes < least) {
+          least = passes;
+          sh.l3c = l;
+        }
+      }
+    }
     if (!fits(sh)) return set_err(c, PW_EINVAL, "H|psi> working set does not fit in LDS for this mesh");
     return launch_shape<T, N, WC>(c, sel, psi, hpsi, st, sh, vscratch);
   }
