@@ -35,6 +35,7 @@
 #include <string>
 #include <type_traits>
 
+#include "hpsi_dense_shape.hpp"
 #include "internal.hpp"
 
 namespace mkpw {
@@ -71,8 +72,7 @@ struct Mf<float> {
   static __device__ __forceinline__ float mul4(float, float, float c) { return c; }  // not used
 };
 
-constexpr size_t kLdsPerCu = 160 * 1024;
-constexpr int kCus = 256;
+constexpr int kGS = kDenseGS, kTS = kDenseTS;
 
 // y, negated where s is negative
 __device__ __forceinline__ float flip(float y, int s) { return __int_as_float(__float_as_int(y) ^ (s & 0x80000000)); }
@@ -100,24 +100,6 @@ template <int N>
 using ic = std::integral_constant<int, N>;
 
 constexpr int kMaxProjDense = 16;
-
-// plane waves of psi staged in LDS at a time: few where two workgroups share a
-// CU's LDS and a chunk has work enough to cover the next one's loads, more for
-// the small row blocks of launches that leave the chip part empty
-constexpr int dense_kc(int nw, int ngm, int rt) {
-  return rt <= 2 ? (ngm == 1 ? 128 : ngm == 2 ? 64 : 32) : nw == 4 && ngm == 3 ? 16 : 32;
-}
-// Reals of a staged row of psi.  A plane wave takes three, (-im, re, im), so that
-// a lane reads its two columns (b2, b1 of the products below) as two neighbours
-// and selects nothing: vector instructions take the matrix cores' issue slots
-// (one between two FP64 products costs 6 cycles of 65, eight cost 20).  The pad
-// of 32 bytes spreads the rows of a step over the banks.
-template <class T>
-__host__ __device__ constexpr int dense_bs(int nw, int ngm, int rt) {
-  return 3 * dense_kc(nw, ngm, rt) + 32 / (int)sizeof(T);
-}
-constexpr int kGS = 20;  // stride of gamma's rows, likewise
-constexpr int kTS = 17;  // stride of the rows of a transposed output tile
 
 template <class T>
 struct DenseArgs {
@@ -148,29 +130,6 @@ __device__ __forceinline__ int box_lin(int key, int s2, int s3) {
   return (((key >> 20) & 1023) * s2 + ((key >> 10) & 1023)) * s3 + (key & 1023);
 }
 
-// LDS of a workgroup in bytes: the box, staged psi, D, the column offsets, the
-// vector list; after the sum over G the projector sums, lambda and gamma, then
-// the output tiles, take the place of the box and of psi
-struct DenseLds {
-  size_t buf, dl, wcol, slot, bytes;
-};
-template <class T>
-__host__ __device__ constexpr DenseLds dense_lds(int nw, int ngm, int rt, int npwx, int nhalf, int nproj, int nall) {
-  const size_t cs = sizeof(cplx<T>), nb = 8 * (size_t)ngm;
-  const size_t box = ((size_t)nhalf * cs + 15) / 16 * 16, buf = 2 * nb * dense_bs<T>(nw, ngm, rt) * sizeof(T);
-  const size_t proj = nall > 0 ? ((size_t)nw * 16 + 16 + kGS) * nb * cs : 0, tile = (size_t)nw * nb * kTS * cs;
-  size_t work = box + buf;
-  if (proj > work) work = proj;
-  if (tile > work) work = tile;
-  DenseLds L{};
-  L.buf = box;
-  L.dl = work;
-  L.wcol = L.dl + (size_t)nproj * nproj * cs;
-  L.slot = L.wcol + sizeof(int) * ((size_t)npwx + 64);
-  L.bytes = L.slot + sizeof(int) * (nb + 4);
-  return L;
-}
-
 // One workgroup of NW waves: one k, up to 8 NGM of its selected vectors, up to
 // 16 NW RTM rows G'.
 template <class T, int NW, int NGM, int RTM>
@@ -178,7 +137,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     DenseArgs<T> a) {
   using M = Mf<T>;
   typedef typename M::acc acc_t;
-  constexpr int NB = 8 * NGM, KC = dense_kc(NW, NGM, RTM), BS = dense_bs<T>(NW, NGM, RTM), NT = NW * 64;
+  constexpr int NB = 8 * NGM, KC = dense_kc(NW, NGM, RTM), BS = dense_bs(NW, NGM, RTM, sizeof(T)), NT = NW * 64;
   constexpr int CS = (int)sizeof(cplx<T>);
   constexpr int kSteps = KC / 4;
   constexpr int kFetch = (NB * KC + NT - 1) / NT;  // staged values per work-item
@@ -188,7 +147,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   constexpr int kL = (kSteps + NW - 1) / NW;  // steps of a chunk that a wave sums for the projectors
   extern __shared__ __align__(16) char smem[];
   const int npwx = a.npwx, nproj = a.nproj, nall = nproj + a.nextra;
-  const DenseLds L = dense_lds<T>(NW, NGM, RTM, npwx, a.nhalf, nproj, nall);
+  const DenseLds L = dense_lds(sizeof(T), NW, NGM, RTM, npwx, a.nhalf, nproj, nall);
   T* buf = reinterpret_cast<T*>(smem + L.buf);  // [2][NB][BS]
   int* wcol = reinterpret_cast<int*>(smem + L.wcol);  // byte offset of each column G, past npw that of G = 0
   int* slot = reinterpret_cast<int*>(smem + L.slot);  // [NB] the selected vectors, then their number
@@ -246,11 +205,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   for (int q = 0; q < kFetch; ++q) {
     const int b = (tid + q * NT) / KC;
     son[q] = b < nact;
-    src[q] = a.psi + vec(son[q] ? b : 0) + (tid & (KC - 1));
+    src[q] = a.psi + vec(son[q] ? b : 0);
   }
   auto fetch = [&](int c, cplx<T>(&x)[kFetch]) {
+    const int g = dense_psi_index(c, KC, tid & (KC - 1), npw);
 #pragma unroll
-    for (int q = 0; q < kFetch; ++q) x[q] = src[q][c * KC];
+    for (int q = 0; q < kFetch; ++q) x[q] = src[q][g];
   };
   auto store = [&](int c, const cplx<T>(&x)[kFetch]) {
     const bool in = c * KC + (tid & (KC - 1)) < npw;
@@ -293,7 +253,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
     }
     cplx<T>* dl = reinterpret_cast<cplx<T>*>(smem + L.dl);
     for (int e = tid; e < nproj * nproj; e += NT) dl[e] = a.dij[e];
-    for (int j = tid; j < npwx + 64; j += NT) wcol[j] = box_lin(key[j < npw ? j : 0], a.s2, a.s3) * CS;
+    for (int j = tid; j < dense_ncol(KC, npwx); j += NT) wcol[j] = box_lin(key[j < npw ? j : 0], a.s2, a.s3) * CS;
   }
 #pragma unroll
   for (int i = 0; i < RTM; ++i) prow[i] = box_lin(prow[i], a.s2, a.s3) * CS;
@@ -318,9 +278,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
   auto sum_g = [&](auto nf, auto nq) {
     constexpr int NF = decltype(nf)::value, NQ = decltype(nq)::value, NG = NF + NQ;
     constexpr int G4 = NF < NGM ? NF : 0;  // the group of the sets
-    // steps an entry of the box is read ahead of its use: one where a step has
-    // products enough to cover the read, more for a small block
-    constexpr int AH = NG * RTM <= 2 ? 4 : NG * RTM <= 4 ? 2 : 1;
+    constexpr int AH = dense_steps_ahead(NG, RTM);
     cplx<T> v[AH][RTM];
     int sg[AH][RTM];
     // V is real, so V~(-d) is the conjugate of V~(d): the box holds one half,
@@ -620,7 +578,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 
 template <class T, int NW, int NGM, int RTM>
 pw_status launch_inst(pw_ctx* c, DenseArgs<T>& a, hipStream_t st) {
-  const size_t lds = dense_lds<T>(NW, NGM, RTM, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra).bytes;
+  const size_t lds = dense_lds(sizeof(T), NW, NGM, RTM, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra).bytes;
   const void* kern = (const void*)hpsi_dense_kernel<T, NW, NGM, RTM>;
   pw_status s = ensure_lds_limit(c, kern, lds);
   if (s != PW_OK) return s;
@@ -674,26 +632,8 @@ pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hi
   a.psi = (const cplx<T>*)psi;
   a.hpsi = (cplx<T>*)hpsi;
   if ((long)c->nk * sel.nvec <= 0) return PW_OK;
-  const int groups = (sel.nvec + 7) / 8;
-  const int tiles = std::max(1, (c->npwmax + 15) / 16);
-  auto lds = [&](int nw, int ngm, int rt) { return dense_lds<T>(nw, ngm, rt, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra).bytes; };
-  // as many vectors per workgroup as fit (each entry of the box that is read
-  // serves them all); two workgroups of four waves per CU where two fit, else
-  // one of eight
-  int ngm = std::min(3, groups);
-  while (ngm > 1 && lds(8, ngm, 4) > kLdsPerCu) --ngm;
-  int nbt = (groups + ngm - 1) / ngm;
-  const int nw = lds(4, ngm, 4) * 2 <= kLdsPerCu ? 4 : 8;
-  const int rmax = nw == 8 ? 4 : fp64 ? (ngm == 3 ? 5 : 6) : 8;
-  int nsplit = (tiles + nw * rmax - 1) / (nw * rmax);
-  // a launch that leaves the chip part empty takes fewer rows per workgroup,
-  // then fewer vectors
-  const long fill = kCus * (8 / nw);
-  while ((long)c->nk * nbt * nsplit < fill && nsplit * nw < tiles) ++nsplit;
-  while ((long)c->nk * nbt * nsplit < fill && nbt < groups) ++nbt;
-  ngm = (groups + nbt - 1) / nbt;
-  int rt = (tiles + nsplit * nw - 1) / (nsplit * nw);
-  if (lds(nw, ngm, rt) > kLdsPerCu) rt = 3;  // the smaller staging of larger blocks
+  const auto [nw, ngm, rt, nbt, nsplit] =
+      dense_shape(sizeof(T), c->nk, sel.nvec, c->npwmax, a.npwx, a.nhalf, a.nproj, a.nproj + a.nextra);
   a.nbt = nbt;
   a.nsplit = nsplit;
   const long ntask = (long)c->nk * nbt * nsplit;
@@ -715,8 +655,8 @@ pw_status launch_t(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, hi
 int hpsi_dense_box(const pw_ctx* c) {
   const long n = (long)(2 * c->wx - 1) * (2 * c->wy - 1) * (2 * c->wz - 1);
   const long half = (n + 1) / 2;
-  if (half > (long)(kLdsPerCu / sizeof(cplx<double>))) return 0;
-  return dense_lds<double>(8, 1, 3, c->npwx, (int)half, kMaxProjDense, kMaxProjDense).bytes <= kLdsPerCu ? (int)half : 0;
+  if (half > (long)(kDenseLdsPerCu / sizeof(cplx<double>))) return 0;
+  return dense_lds(8, 8, 1, 3, c->npwx, (int)half, kMaxProjDense, kMaxProjDense).bytes <= kDenseLdsPerCu ? (int)half : 0;
 }
 
 // Whether H|psi> of this call takes the dense product rather than the transforms
