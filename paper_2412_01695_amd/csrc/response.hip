@@ -54,20 +54,25 @@ __device__ __forceinline__ int wrap(int d, int n) {
 
 // one axis of a separable DFT of the n1 x n2 x n3 mesh (C order, l3 fastest):
 // out(.., l, ..) = scale * sum_j in(.., j, ..) exp(sign 2 pi i j l / n_axis).
-// The n roots of unity are formed once per workgroup, in LDS: sines and cosines
-// per term were most of its time (30^3: 17.6 us a pass before, 8.0 now, a chain
-// of loads that a hundred workgroups cannot hide).
-constexpr int kDftMax = 512;  // longest axis (the largest mesh that pw_set_cutoff takes)
+// With TABLE the n roots of unity are formed once per workgroup, in LDS (sized by
+// the launch): sines and cosines per term were most of its time (30^3: 17.6 us a
+// pass with them, 8.0 so, a chain of loads that a hundred workgroups cannot hide).
+constexpr int kDftTable = 4096;  // longest axis with a table: the 64 KB any launch may take
+template <bool TABLE>
 __global__ __launch_bounds__(256) void mesh_dft_axis_kernel(const cd* __restrict__ in, cd* __restrict__ out, int n1,
                                                             int n2, int n3, int axis, int sign, double scale) {
-  __shared__ cd tw[kDftMax];
+  extern __shared__ __align__(16) char smem[];
+  cd* tw = reinterpret_cast<cd*>(smem);
   const int n = axis == 0 ? n1 : axis == 1 ? n2 : n3;
-  for (int j = threadIdx.x; j < n; j += 256) {
+  auto root = [&](int j) {
     double s, c;
     sincospi(2.0 * j / n, &s, &c);
-    tw[j] = {c, sign * s};
+    return cd{c, sign * s};
+  };
+  if constexpr (TABLE) {
+    for (int j = threadIdx.x; j < n; j += 256) tw[j] = root(j);
+    __syncthreads();
   }
-  __syncthreads();
   const long total = (long)n1 * n2 * n3;
   const long e = (long)blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
@@ -84,7 +89,7 @@ __global__ __launch_bounds__(256) void mesh_dft_axis_kernel(const cd* __restrict
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       if (j0 + u < n) {
-        const cd w = tw[t];
+        const cd w = TABLE ? tw[t] : root(t);
         sr += v[u].x * w.x - v[u].y * w.y;
         si += v[u].x * w.y + v[u].y * w.x;
         t += l;
@@ -685,17 +690,27 @@ pw_status check_pair(pw_ctx* ckq, const pw_ctx* ck) {
   return PW_OK;
 }
 
+// One axis of the mesh transform.  pw_set_cutoff bounds the axes of a mesh it is
+// given (512), not of one it chooses, which a long cell makes longer.
+void launch_mesh_dft(pw_ctx* c, const cd* in, cd* out, int axis, int sign, double scale, hipStream_t st) {
+  const int n1 = c->fft[0], n2 = c->fft[1], n3 = c->fft[2], n = c->fft[axis];
+  const dim3 grid((unsigned)(((long)n1 * n2 * n3 + 255) / 256));
+  if (n <= kDftTable)
+    hipLaunchKernelGGL(mesh_dft_axis_kernel<true>, grid, dim3(256), sizeof(cd) * n, st, in, out, n1, n2, n3, axis, sign,
+                       scale);
+  else
+    hipLaunchKernelGGL(mesh_dft_axis_kernel<false>, grid, dim3(256), 0, st, in, out, n1, n2, n3, axis, sign, scale);
+}
+
 // dV~ = forward transform of dV(r) with 1/N_r (Eq. fwFFT), on the device
 pw_status transform_dv(pw_ctx* c, const double* dv_host, cd* dvt, cd* tmp, hipStream_t st) {
-  const int n1 = c->fft[0], n2 = c->fft[1], n3 = c->fft[2];
-  const long nr = (long)n1 * n2 * n3;
+  const long nr = (long)c->fft[0] * c->fft[1] * c->fft[2];
   HostStage hs(c, st);
   MKPW_TRY(hs.init(sizeof(cd) * nr, 0));
   MKPW_HIP(c, hs.up(tmp, (const cd*)dv_host, (size_t)nr));
-  const dim3 grid((unsigned)((nr + 255) / 256));
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, tmp, dvt, n1, n2, n3, 0, -1, 1.0);
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, dvt, tmp, n1, n2, n3, 1, -1, 1.0);
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, tmp, dvt, n1, n2, n3, 2, -1, 1.0 / (double)nr);
+  launch_mesh_dft(c, tmp, dvt, 0, -1, 1.0, st);
+  launch_mesh_dft(c, dvt, tmp, 1, -1, 1.0, st);
+  launch_mesh_dft(c, tmp, dvt, 2, -1, 1.0 / (double)nr, st);
   MKPW_TRY(check_launch(c, "mesh_dft", st));
   return PW_OK;
 }
@@ -911,9 +926,9 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
                      nchunk, D[0], D[1], D[2], n1, n2, n3, Fc);
   hipLaunchKernelGGL(sum_chunks_kernel, grid, dim3(256), 0, st, Fc, nchunk, nr, F);
   // drho(r) = sum_f F(f) exp(+2 pi i f.l / N)
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, F, tmp, n1, n2, n3, 0, 1, 1.0);
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, tmp, F, n1, n2, n3, 1, 1, 1.0);
-  hipLaunchKernelGGL(mesh_dft_axis_kernel, grid, dim3(256), 0, st, F, (cd*)drho_r, n1, n2, n3, 2, 1, 1.0);
+  launch_mesh_dft(ckq, F, tmp, 0, 1, 1.0, st);
+  launch_mesh_dft(ckq, tmp, F, 1, 1, 1.0, st);
+  launch_mesh_dft(ckq, F, (cd*)drho_r, 2, 1, 1.0, st);
   MKPW_TRY(check_launch(ckq, "drho", st));
   MKPW_HIP(ckq, hipStreamSynchronize(st));
   return PW_OK;
