@@ -107,6 +107,10 @@ typedef double mf64x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ mf64x4 mfma_16x16x4(double a, double b, mf64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+// C - A B: of an FP64 product the last field negates operands, its first bit A
+__device__ __forceinline__ mf64x4 mfma_16x16x4_sub(double a, double b, mf64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
+}
 
 // Linear offset of a Miller triple in a box of sizes (., s2, s3): m1 s2 s3 +
 // m2 s3 + m3.  Differences of such offsets are offsets of Miller differences,
@@ -463,6 +467,8 @@ __global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
 }
 
 constexpr int kRhoWaves = 16;  // waves per workgroup of drho_mfma_kernel
+constexpr size_t kRhoLds = 160 * 1024;  // the most a workgroup's bins and tables take
+constexpr int kRhoOwn = (int)(kRhoLds / (sizeof(cd) * kRhoWaves * 64));  // bins a work-item keeps the sum of
 constexpr int kDrhoWgs = 256;  // its workgroups that run at once, one per CU
 
 // Per k: bins F_k(d) += 4 w_k M(G1, G2) over the pairs with d = m_G2 - m_G1 -
@@ -479,8 +485,11 @@ constexpr int kDrhoWgs = 256;  // its workgroups that run at once, one per CU
 // staged in LDS after the bins.  The bins fill most of a CU's LDS, so a
 // workgroup is as wide as a CU takes to hide latency, and it keeps its bins for
 // all its units (run u % nrun of the tiles of k = u / nrun), the tables of the
-// next k filled under the tiles of this one.
-template <int NBS>
+// next k filled under the tiles of this one.  MANY: units of more than one k; each
+// k is summed by itself, as one workgroup per k would, and the finished k's sums
+// are kept in registers (one running sum of eight k: error 1.4e-15 of the largest
+// value at 2048 k x 8 bands against 1.0e-15 so, 498 us both).
+template <int NBS, bool MANY>
 __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
     int nk, int nrun, int nbnd, const double* __restrict__ wk, const int* __restrict__ npw1, const int* __restrict__ key1, int npwx1,
     const cd* __restrict__ u1, const int* __restrict__ npw2, const int* __restrict__ key2, int npwx2,
@@ -503,6 +512,13 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
       t1[npwx1 + g] = miller_lin(key2[(long)kk * npwx2 + g], D2, D3);
   };
   for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) bre[e] = bim[e] = 0.0;
+  // the finished k's sums of bins threadIdx.x + 1024 i
+  constexpr int kOwn = MANY ? kRhoOwn : 1;
+  cd sum[kOwn];
+  if constexpr (MANY) {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) sum[i] = {0.0, 0.0};
+  }
   // this workgroup's share of the nk nrun units (a k's tiles in nrun runs)
   const long nunit = (long)nk * nrun;
   int u = (int)(nunit * blockIdx.x / gridDim.x);
@@ -527,7 +543,7 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
     constexpr int NR = NBS > 0 ? NBS : 1;
     // with the A entries in registers the weight f is folded into them
     const double fb = NBS > 0 ? 1.0 : f;
-    double arc[NR], aic[NR], naic[NR], brc[NR], bic[NR];
+    double arc[NR], aic[NR], brc[NR], bic[NR];
     int o1v[4];
     // B entries of tile column jt (register path): unconditional loads from
     // clamped addresses; a band past nbnd meets a zeroed A entry, and a column
@@ -549,7 +565,7 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
     int cur = -1;
     if (NBS > 0 && t0 < t1) fetch_b(jt);
     // the next k's tables under this k's tiles
-    const bool turn = u + 1 < uend && (u + 1) / nrun != k;
+    const bool turn = MANY && u + 1 < uend && (u + 1) / nrun != k;
     if (turn) tables(k + 1, which ^ 1);
     for (int t = t0; t < t1; ++t) {
       const int g1 = it * 16 + l16, g2 = jt * 16 + l16;  // this lane's A row and B column
@@ -569,7 +585,6 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
             const cd a = a1[(long)(nu < nbnd ? nu : 0) * npwx1];
             arc[s] = nu < nbnd ? f * a.x : 0.0;
             aic[s] = nu < nbnd ? -f * a.y : 0.0;  // f conj(u1); rows past the sphere are never binned
-            naic[s] = -aic[s];
           }
           // box offsets of this row's G1 (rows past the sphere get a bin
           // outside the box)
@@ -583,7 +598,7 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
   #pragma unroll
         for (int s = 0; s < NR; ++s) {
           cr = mfma_16x16x4(arc[s], brc[s], cr);
-          cr = mfma_16x16x4(naic[s], bic[s], cr);
+          cr = mfma_16x16x4_sub(aic[s], bic[s], cr);
           ci = mfma_16x16x4(arc[s], bic[s], ci);
           ci = mfma_16x16x4(aic[s], brc[s], ci);
         }
@@ -601,7 +616,7 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
           }
           const double ar = a.x, ai = -a.y;  // conj(u1)
           cr = mfma_16x16x4(ar, b.x, cr);
-          cr = mfma_16x16x4(-ai, b.y, cr);
+          cr = mfma_16x16x4_sub(ai, b.y, cr);
           ci = mfma_16x16x4(ar, b.y, ci);
           ci = mfma_16x16x4(ai, b.x, ci);
         }
@@ -627,14 +642,34 @@ __global__ __launch_bounds__(kRhoWaves * 64) void drho_mfma_kernel(
       it = in;
       jt = jn;
     }
-    if (turn) {
-      __syncthreads();  // the other tables are whole, these are free
-      which ^= 1;
+    if constexpr (MANY) {
+      if (turn) {
+        __syncthreads();  // the other tables are whole, these are free; so are the k's bins
+        which ^= 1;
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+          const int e = threadIdx.x + i * kRhoWaves * 64;
+          if (e < nbin) {
+            sum[i].x += bre[e];
+            sum[i].y += bim[e];
+            bre[e] = bim[e] = 0.0;
+          }
+        }
+        __syncthreads();
+      }
     }
   }
   __syncthreads();
   cd* dst = part + ((long)blockIdx.x * D1 + x0) * D2 * D3;
-  for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) dst[e] = {bre[e], bim[e]};
+  if constexpr (MANY) {
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      const int e = threadIdx.x + i * kRhoWaves * 64;
+      if (e < nbin) dst[e] = {sum[i].x + bre[e], sum[i].y + bim[e]};
+    }
+  } else {
+    for (int e = threadIdx.x; e < nbin; e += kRhoWaves * 64) dst[e] = {bre[e], bim[e]};
+  }
 }
 
 // F_c(l) = sum over the k of chunk c (k = c, c + nchunk, ...) of the part[k]
@@ -873,7 +908,7 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
   // One origin for all k, so that a workgroup bins runs of several k into one
   // box, unless that box takes more slices than a box per k (k-points far
   // apart in Miller space): the pair products are formed once per slice
-  const long na = slice(DA, 2, 160 * 1024);
+  const long na = slice(DA, 2, kRhoLds);
   const bool one = na > 0 && (DA[0] + na - 1) / na <= (D[0] + nx - 1) / nx;
   if (one) {
     nx = na;
@@ -905,20 +940,20 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
   MKPW_HIP(ckq, hs.up(d_org, org.data(), org.size()));
   MKPW_HIP(ckq, hs.up(d_w, wk, (size_t)nk));
   const int nbs = nbnd <= 8 ? 2 : nbnd <= 16 ? 4 : 0;  // band steps held in registers
-  const void* kern = nbs == 2 ? (const void*)drho_mfma_kernel<2>
-                     : nbs == 4 ? (const void*)drho_mfma_kernel<4> : (const void*)drho_mfma_kernel<0>;
+  const bool many = npart < (long)nk * nrun;
+  const auto kern = many ? (nbs == 2   ? drho_mfma_kernel<2, true>
+                            : nbs == 4 ? drho_mfma_kernel<4, true>
+                                       : drho_mfma_kernel<0, true>)
+                         : (nbs == 2   ? drho_mfma_kernel<2, false>
+                            : nbs == 4 ? drho_mfma_kernel<4, false>
+                                       : drho_mfma_kernel<0, false>);
   for (int x0 = 0; x0 < D[0]; x0 += (int)nx) {
     const int nxx = std::min((int)nx, D[0] - x0);
     const size_t lds = per_x * nxx + tiles + 2 * sizeof(double);
-    MKPW_TRY(ensure_lds_limit(ckq, kern, lds));
-#define MKPW_DRHO(NBS)                                                                                              \
-  hipLaunchKernelGGL(drho_mfma_kernel<NBS>, dim3((unsigned)npart), dim3(kRhoWaves * 64), lds, st, nk, nrun, \
-                     nbnd, d_w, ck->d_npw, ck->d_mkey, ck->npwx, (const cd*)psi_k, ckq->d_npw, ckq->d_mkey,         \
-                     ckq->npwx, (const cd*)dpsi_kq, d_org, D[0], D[1], D[2], x0, nxx, part)
-    if (nbs == 2) MKPW_DRHO(2);
-    else if (nbs == 4) MKPW_DRHO(4);
-    else MKPW_DRHO(0);
-#undef MKPW_DRHO
+    MKPW_TRY(ensure_lds_limit(ckq, (const void*)kern, lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)npart), dim3(kRhoWaves * 64), lds, st, nk, nrun, nbnd, d_w, ck->d_npw,
+                       ck->d_mkey, ck->npwx, (const cd*)psi_k, ckq->d_npw, ckq->d_mkey, ckq->npwx, (const cd*)dpsi_kq,
+                       d_org, D[0], D[1], D[2], x0, nxx, part);
     MKPW_TRY(check_launch(ckq, "drho_pairs", st));
   }
   const dim3 grid((unsigned)((nr + 255) / 256));
