@@ -78,7 +78,9 @@ void pw_destroy(pw_ctx* ctx);
 const char* pw_last_error(const pw_ctx* ctx);
 
 /* Options: "hbm_budget_bytes" (0 = none; larger device workspaces fail with
- * PW_ENOMEM, the paper's memgpu input of Sec. 5.1), "davidson_basis_factor"
+ * PW_ENOMEM, the paper's memgpu input of Sec. 5.1; what a context keeps of its
+ * potential for H besides V itself, under 1 MB, is kept only where it fits and
+ * takes no room from later calls), "davidson_basis_factor"
  * (maximum Davidson basis in units of nbnd, default 4, Sec. 5.3), "trace"
  * (nonzero: synchronise and check after every launch), "hpsi_variant"
  * (0 = autotuned on first use, 1 = one work-item per FFT line, 2 = two lanes

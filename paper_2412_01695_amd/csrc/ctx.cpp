@@ -33,12 +33,13 @@ pw_status set_err(pw_ctx* c, pw_status s, const std::string& msg) {
   return s;
 }
 
-pw_status dev_alloc(pw_ctx* c, size_t bytes, void** out) {
+pw_status dev_alloc(pw_ctx* c, size_t bytes, void** out, bool extra) {
   *out = nullptr;
   if (bytes == 0) return PW_OK;
   if (c->hbm_budget > 0) {
     size_t used = 0;
-    for (auto& m : c->owned) used += m.bytes;
+    for (auto& m : c->owned)
+      if (extra || !m.extra) used += m.bytes;
     if ((int64_t)(used + bytes) > c->hbm_budget)
       return set_err(c, PW_ENOMEM, "HBM budget exceeded: need " + std::to_string(used + bytes) +
                                        " bytes, budget " + std::to_string(c->hbm_budget));
@@ -51,7 +52,7 @@ pw_status dev_alloc(pw_ctx* c, size_t bytes, void** out) {
     (void)hipGetLastError();
     return set_err(c, PW_ENOMEM, std::string("hipMallocAsync failed: ") + hipGetErrorString(e));
   }
-  c->owned.push_back({p, bytes});
+  c->owned.push_back({p, bytes, extra});
   *out = p;
   return PW_OK;
 }

@@ -38,8 +38,10 @@ struct DevBufs {
   explicit DevBufs(pw_ctx* cc) : c(cc) {}
   DevBufs(const DevBufs&) = delete;
   DevBufs& operator=(const DevBufs&) = delete;
-  ~DevBufs() {
+  ~DevBufs() { release(); }
+  void release() {
     for (void* p : ptrs) dev_free(c, p);
+    ptrs.clear();
   }
   template <class T>
   pw_status get(size_t n, T** out) {

@@ -133,7 +133,7 @@ void hpsi_potential_build(pw_ctx* c) {
   const std::string err = c->err;
   const long most = std::max({d1 * n * n, d1 * d2 * n, d1 * d2 * d3, nr});
   void *a = nullptr, *b = nullptr;
-  auto get = [&](long bytes, void** p) { return dev_alloc(c, (size_t)bytes, p) == PW_OK; };
+  auto get = [&](long bytes, void** p) { return dev_alloc(c, (size_t)bytes, p, true) == PW_OK; };
   bool ok = get(sizeof(cd) * most, &a) && get(sizeof(cd) * most, &b) && get(sizeof(double) * nr, &c->d_vk64) &&
             get(sizeof(float) * nr, &c->d_vk32) && get(sizeof(cd) * half, &c->d_box64) &&
             get(sizeof(cplx<float>) * half, &c->d_box32);

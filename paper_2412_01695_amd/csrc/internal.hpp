@@ -73,6 +73,7 @@ struct CombArgs {
 struct DevMem {
   void* p = nullptr;
   size_t bytes = 0;
+  bool extra = false;
 };
 
 }  // namespace mkpw
@@ -168,7 +169,12 @@ struct pw_ctx {
 namespace mkpw {
 
 pw_status set_err(pw_ctx* c, pw_status s, const std::string& msg);
-pw_status dev_alloc(pw_ctx* c, size_t bytes, void** out);
+// Device memory from the context's stream-ordered pool, within its budget.  With
+// `extra`, memory that the context can do without (what it keeps of the potential
+// for the faster H|psi> paths, under 1 MB): allocated only if it fits beside
+// everything held, and not counted against what is allocated afterwards, so that
+// no other call is refused for it.
+pw_status dev_alloc(pw_ctx* c, size_t bytes, void** out, bool extra = false);
 void dev_free(pw_ctx* c, void* p);
 // c->pin with at least `bytes` (the context's stream is synchronised first)
 pw_status host_pinned(pw_ctx* c, size_t bytes, void** out);

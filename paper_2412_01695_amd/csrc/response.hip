@@ -880,16 +880,16 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
   const int n1 = ckq->fft[0], n2 = ckq->fft[1], n3 = ckq->fft[2];
   const long nr = (long)n1 * n2 * n3;
   // per-k origin of the Miller difference m(k+q) - m(k) and the size that holds
-  // every k's box from its own origin (D) or all k from one origin (DA); from
+  // every k's box from its own origin (DK) or all k from one origin (DA); from
   // each sphere's Miller bounds, kept by pw_set_kpoints
   std::vector<int> org(3 * (size_t)nk);
-  int D[3] = {1, 1, 1}, lo[3], DA[3];
+  int DK[3] = {1, 1, 1}, lo[3], DA[3];
   for (int a = 0; a < 3; ++a) {
     int dlo = 1 << 20, dhi = -(1 << 20);
     for (int k = 0; k < nk; ++k) {
       const int l = ckq->mlo[3 * k + a] - ck->mhi[3 * k + a], h = ckq->mhi[3 * k + a] - ck->mlo[3 * k + a];
       org[3 * k + a] = l;
-      D[a] = std::max(D[a], h - l + 1);
+      DK[a] = std::max(DK[a], h - l + 1);
       dlo = std::min(dlo, l);
       dhi = std::max(dhi, h);
     }
@@ -903,38 +903,53 @@ extern "C" pw_status pw_drho(pw_ctx* ckq, const pw_ctx* ck, int nbnd, const doub
     const size_t per_x = 2 * sizeof(double) * (size_t)d[1] * d[2], rest = ntab * table + 16 + 2 * sizeof(double);
     return rest < lds ? (long)std::min<size_t>(d[0], (lds - rest) / per_x) : 0;
   };
-  long nx = slice(D, 1, 150 * 1024);
-  if (nx < 1) return set_err(ckq, PW_EINVAL, "drho: plane-wave spheres too large for the bins");
+  const long nxk = slice(DK, 1, 150 * 1024);
+  if (nxk < 1) return set_err(ckq, PW_EINVAL, "drho: plane-wave spheres too large for the bins");
   // One origin for all k, so that a workgroup bins runs of several k into one
   // box, unless that box takes more slices than a box per k (k-points far
   // apart in Miller space): the pair products are formed once per slice
   const long na = slice(DA, 2, kRhoLds);
-  const bool one = na > 0 && (DA[0] + na - 1) / na <= (D[0] + nx - 1) / nx;
-  if (one) {
-    nx = na;
-    for (int a = 0; a < 3; ++a) {
-      D[a] = DA[a];
-      for (int k = 0; k < nk; ++k) org[3 * k + a] = lo[a];
-    }
-  }
+  bool one = na > 0 && (DA[0] + na - 1) / na <= (DK[0] + nxk - 1) / nxk;
   // runs per k: some four for each CU, so that uneven shares differ little,
   // but eight tiles or more per wave (each workgroup writes a box, which the sum
   // over boxes reads again); with a box per k one for each CU
   const int ntile = ((ck->npwmax + 15) / 16) * ((ckq->npwmax + 15) / 16);
-  const int nrun = std::max(1, std::min(one ? (4 * kDrhoWgs + nk - 1) / nk : kDrhoWgs / nk, ntile / (8 * kRhoWaves)));
-  const int npart = one ? (int)std::min<long>((long)nk * nrun, kDrhoWgs) : nk * nrun;
-  const size_t per_x = 2 * sizeof(double) * (size_t)D[1] * D[2], tiles = (one ? 2 : 1) * table + 16;
+  int nrun = std::max(1, std::min(one ? (4 * kDrhoWgs + nk - 1) / nk : kDrhoWgs / nk, ntile / (8 * kRhoWaves)));
   DevBufs b(ckq);
   cd *part, *F, *tmp, *Fc;
   int* d_org;
   double* d_w;
-  const int nchunk = std::min((npart + 7) / 8, 64);
-  MKPW_TRY(b.get((size_t)npart * D[0] * D[1] * D[2], &part));
-  MKPW_TRY(b.get((size_t)nchunk * nr, &Fc));
-  MKPW_TRY(b.get((size_t)nr, &F));
-  MKPW_TRY(b.get((size_t)nr, &tmp));
-  MKPW_TRY(b.get((size_t)3 * nk, &d_org));
-  MKPW_TRY(b.get((size_t)nk, &d_w));
+  int npart = 0, nchunk = 0;
+  auto arrays = [&]() -> pw_status {
+    const int* d = one ? DA : DK;
+    npart = one ? (int)std::min<long>((long)nk * nrun, kDrhoWgs) : nk * nrun;
+    nchunk = std::min((npart + 7) / 8, 64);
+    MKPW_TRY(b.get((size_t)npart * d[0] * d[1] * d[2], &part));
+    MKPW_TRY(b.get((size_t)nchunk * nr, &Fc));
+    MKPW_TRY(b.get((size_t)nr, &F));
+    MKPW_TRY(b.get((size_t)nr, &tmp));
+    MKPW_TRY(b.get((size_t)3 * nk, &d_org));
+    return b.get((size_t)nk, &d_w);
+  };
+  const std::string err = ckq->err;
+  pw_status got = arrays();
+  if (got == PW_ENOMEM && (one || nrun > 1)) {
+    // a box per k, one workgroup each, may take less memory (few k)
+    b.release();
+    one = false;
+    nrun = 1;
+    got = arrays();
+    if (got == PW_OK) ckq->err = err;
+  }
+  MKPW_TRY(got);
+  int D[3];
+  for (int a = 0; a < 3; ++a) {
+    D[a] = one ? DA[a] : DK[a];
+    if (one)
+      for (int k = 0; k < nk; ++k) org[3 * k + a] = lo[a];
+  }
+  const long nx = one ? na : nxk;
+  const size_t per_x = 2 * sizeof(double) * (size_t)D[1] * D[2], tiles = (one ? 2 : 1) * table + 16;
   HostStage hs(ckq, st);
   MKPW_TRY(hs.init(sizeof(int) * org.size() + sizeof(double) * nk + 512, 0));
   MKPW_HIP(ckq, hs.up(d_org, org.data(), org.size()));
