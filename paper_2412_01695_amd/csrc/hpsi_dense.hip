@@ -660,34 +660,14 @@ int hpsi_dense_box(const pw_ctx* c) {
 }
 
 // Whether H|psi> of this call takes the dense product rather than the transforms
-// on the smallest mesh.  Measured over cutoffs of 15 to 52 Ry, 2 to 1200 k and 1
-// to 24 vectors (us, transforms / dense; npw in brackets):
-//   * each entry of the box is read once per plane-wave pair whatever the vectors,
-//     so few vectors do not pay: FP64, 1200 k [305], 1 vector 60 / 103, 3 vectors
-//     138 / 133, 6 vectors 254 / 169, 24 vectors 881 / 487;
-//   * a workgroup takes a whole k, so few k leave the chip part empty: FP64, 24
-//     vectors [305], 64 k 58 / 69, 300 k 254 / 190; [469] 300 k 384 / 413, 1200 k
-//     1403 / 1032;
-//   * the sum grows as npw^2, the transforms as the window's cube: FP64, 1200 k
-//     x 16 vectors [705] 1842 / 1550, and 20 vectors, of which its LDS holds only
-//     two thirds at a time, 2266 / 2900; complex64, whose transforms take half
-//     the time of FP64 at a quarter of the issue slots: 1200 k x 16 [305] 268 /
-//     181, [469] 437 / 383, x 24 [576] 814 / 840.
+// on the smallest mesh
 bool hpsi_takes_dense(const pw_ctx* c, pw_prec prec, const VecSel& sel, int nextra) {
   if (!c->d_box64 || !c->d_box32) return false;
   if (c->hpsi_variant != 0 || c->hpsi_slab != 0 || c->hpsi_threads != 0) return false;  // a transform shape is asked for
-  if ((c->have_proj ? c->nproj : 0) + nextra > kMaxProjDense) return false;  // lambda is one tile of rows
-  const int npw = c->npwmax, nk = c->nk, nv = sel.nvec;
-  if (npw <= 128) return nv >= 3;
-  if (nv < 6) return false;
-  if (prec == PW_FP64) {
-    if (npw <= 336) return nk >= 256;
-    if (npw <= 640) return nk >= 512;
-    return nk >= 256 && nv <= 16;
-  }
-  if (npw <= 240) return nk >= 256;
-  if (npw <= 336) return nk >= 512;
-  return npw <= 520 && nk >= 1024 && nv >= 14;
+  const int nproj = c->have_proj ? c->nproj : 0;
+  if (nproj + nextra > kMaxProjDense) return false;  // lambda is one tile of rows
+  return dense_faster(prec == PW_FP64 ? 8 : 4, c->nk, sel.nvec, c->npwmax, c->npwx, hpsi_dense_box(c), nproj,
+                      nproj + nextra, c->kmesh ? c->kmesh : c->fft[0], std::max(c->wx, std::max(c->wy, c->wz)));
 }
 
 pw_status launch_hpsi_dense(pw_ctx* c, pw_prec prec, const VecSel& sel, const void* psi, void* hpsi, hipStream_t st,

@@ -59,13 +59,43 @@ int main() {
 """
 
 
-def test_every_shape_reads_in_bounds(tmp_path):
+# real, k, vectors, plane waves, window, projectors, mesh; us of the transforms and of
+# the product.  Launches where one path takes more than the other by a sixth or more.
+TIMED = [
+    (8, 700, 16, 648, 12, 4, 24, 581, 842), (8, 512, 6, 648, 12, 4, 24, 160, 281), (8, 300, 12, 820, 13, 4, 30, 341, 471),
+    (8, 400, 16, 696, 11, 4, 24, 319, 580), (8, 1000, 8, 696, 11, 4, 24, 415, 638), (8, 300, 6, 728, 13, 4, 30, 180, 231),
+    (8, 512, 12, 928, 12, 16, 24, 606, 829), (8, 317, 6, 362, 10, 4, 20, 70, 101),
+    (8, 512, 20, 316, 10, 8, 20, 334, 163), (8, 1728, 24, 490, 11, 4, 24, 1860, 1415), (8, 600, 24, 490, 11, 4, 24, 650, 545),
+    (8, 400, 6, 173, 8, 4, 15, 38, 29), (8, 1000, 16, 728, 13, 16, 30, 2144, 1380), (8, 317, 13, 705, 13, 16, 30, 499, 439),
+    (4, 1000, 6, 571, 12, 4, 24, 147, 267), (4, 1200, 10, 363, 10, 8, 20, 179, 216), (4, 600, 6, 490, 11, 4, 24, 90, 113),
+    (4, 2048, 16, 316, 10, 8, 20, 461, 258), (4, 1728, 24, 490, 11, 4, 24, 902, 748), (4, 1024, 24, 409, 11, 8, 24, 379, 323),
+]
+
+
+def _run(tmp_path, text):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no host C++ compiler")
     src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
-    src.write_text(WALK)
+    src.write_text(text)
     subprocess.run([cxx, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2412_01695_amd", "csrc"), str(src),
                     "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True)
+
+
+def test_every_shape_reads_in_bounds(tmp_path):
+    r = _run(tmp_path, WALK)
     assert r.returncode == 0, r.stdout
+
+
+def test_the_faster_path_is_taken(tmp_path):
+    calls = []
+    for real, nk, nv, npw, w, nproj, mesh, _, _ in TIMED:
+        npwx, nhalf = (npw + 63) // 64 * 64, ((2 * w - 1)**3 + 1) // 2
+        calls.append(f'std::printf("%d ", (int)dense_faster({real}, {nk}, {nv}, {npw}, {npwx}, {nhalf}, {nproj}, {nproj}, '
+                     f'{mesh}, {w}));')
+    r = _run(tmp_path, "#include <cstdio>\n#include \"hpsi_dense_shape.hpp\"\nusing namespace mkpw;\nint main() {\n"
+             + "\n".join(calls) + "\nreturn 0;\n}\n")
+    assert r.returncode == 0
+    for row, took in zip(TIMED, r.stdout.split(), strict=True):
+        assert bool(int(took)) == (row[-1] < row[-2]), row
