@@ -351,6 +351,18 @@ void launch_spsi_tw(pw_ctx* c, const VecSel& sel, const void* psi, void* out, co
 #undef MKPW_SPSI
 }
 
+template <class T, int NP>
+void launch_spsi_any(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
+                     int nproj, const void* beta, const void* q, hipStream_t st) {
+  const int ntask = sel.nvec * c->nk;
+  const int nblk = (ntask + kSThreads / 64 - 1) / (kSThreads / 64);
+  const int per_xcd = (nblk + 7) / 8;
+  const size_t lds = sizeof(cplx<T>) * (size_t)std::max(1, nproj * nproj);
+  hipLaunchKernelGGL((spsi_kernel<T, NP>), dim3(8u * (unsigned)per_xcd), dim3(kSThreads), lds, st,
+                     (const cplx<T>*)psi, (cplx<T>*)out, sel.kstride, sel.nvec, sel.off, sel.cnt, sel.live, c->d_npw,
+                     c->npwx, nproj, (const cplx<T>*)beta, (const cplx<T>*)q, scale, mult, per_xcd, ntask);
+}
+
 template <class T>
 void launch_spsi_t(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
                    int nproj, const void* beta, const void* q, hipStream_t st) {
@@ -363,13 +375,13 @@ void launch_spsi_t(pw_ctx* c, const VecSel& sel, const void* psi, void* out, con
       launch_spsi_tw<T, true>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
     return;
   }
-  const int ntask = sel.nvec * c->nk;
-  const int nblk = (ntask + kSThreads / 64 - 1) / (kSThreads / 64);
-  const int per_xcd = (nblk + 7) / 8;
-  const size_t lds = sizeof(cplx<T>) * (size_t)std::max(1, nproj * nproj);
-  hipLaunchKernelGGL((spsi_kernel<T, kSMaxProj>), dim3(8u * (unsigned)per_xcd), dim3(kSThreads), lds, st,
-                     (const cplx<T>*)psi, (cplx<T>*)out, sel.kstride, sel.nvec, sel.off, sel.cnt, sel.live, c->d_npw,
-                     c->npwx, nproj, (const cplx<T>*)beta, (const cplx<T>*)q, scale, mult, per_xcd, ntask);
+  // longer rows and more projectors: lambda and delta of 32 take the registers that
+  // five waves have with those of 8 (200 k x 20 rows [1088], FP64, 8 projectors: 103
+  // us against 325 with the kernel of 32)
+  if (nproj <= 8)
+    launch_spsi_any<T, 8>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else
+    launch_spsi_any<T, kSMaxProj>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
 }
 
 }  // namespace
