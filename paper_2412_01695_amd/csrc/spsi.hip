@@ -221,13 +221,14 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(TW <=
   }
 }
 
-// ------------------------------------------------------------------ any size
+// ------------------------------------------------------------------ on the vector units
 
-// One wavefront per row, four rows per workgroup: each lane accumulates its
-// plane waves' share of the nproj inner products, DPP sums give every lane all
-// of lambda, every lane forms delta from q (staged in LDS), and writes its
-// plane waves (psi read a second time, from L2).
-template <class T, int NP>
+// NP: nproj rounded up to a multiple of 8 (8 or 32), so that lambda and
+// delta live in registers.  NPL > 0: each lane keeps its NPL plane waves
+// (g = lane + 64 i) of psi in registers, loaded all at once, so the row is read
+// from HBM once with every load in flight together; NPL = 0 (rows longer than
+// 16 x 64) loops over the row and reads psi a second time for the output.
+template <class T, int NP, int NPL>
 __global__ __launch_bounds__(kSThreads) void spsi_kernel(const cplx<T>* psi, cplx<T>* out, long kstride, int nvec,
                                                          const int* __restrict__ off, const int* __restrict__ cnt,
                                                          const int* __restrict__ live, const int* __restrict__ npw_k,
@@ -253,6 +254,15 @@ __global__ __launch_bounds__(kSThreads) void spsi_kernel(const cplx<T>* psi, cpl
   cplx<T>* y = out + row;
   const int npw = npw_k[k];
   const cplx<T>* bk = beta + (long)k * nproj * npwx;
+  constexpr int NC = NPL > 0 ? NPL : 1;
+  cplx<T> xr[NC];
+  if constexpr (NPL > 0) {
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+      const int g = lane + 64 * i;
+      xr[i] = g < npw ? x[g] : cplx<T>{T(0), T(0)};
+    }
+  }
   // lambda_p = sum_G conj(beta_p(G)) psi(G)   (Eq. lambdah), on every lane
   T lr[NP], li[NP];
 #pragma unroll
@@ -267,7 +277,13 @@ __global__ __launch_bounds__(kSThreads) void spsi_kernel(const cplx<T>* psi, cpl
       }
     }
   };
-  for (int g = lane; g < npw; g += 64) accumulate(g, x[g]);
+  if constexpr (NPL > 0) {
+#pragma unroll
+    for (int i = 0; i < NPL; ++i)
+      if (lane + 64 * i < npw) accumulate(lane + 64 * i, xr[i]);
+  } else {
+    for (int g = lane; g < npw; g += 64) accumulate(g, x[g]);
+  }
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     if (p < nproj) {
@@ -313,7 +329,146 @@ __global__ __launch_bounds__(kSThreads) void spsi_kernel(const cplx<T>* psi, cpl
       y[g] = v;
     }
   };
-  for (int g = lane; g < npwx; g += 64) emit(g, g < npw ? x[g] : cplx<T>{T(0), T(0)});
+  if constexpr (NPL > 0) {
+#pragma unroll
+    for (int i = 0; i < NPL; ++i)
+      if (lane + 64 * i < npwx) emit(lane + 64 * i, xr[i]);
+  } else {
+    for (int g = lane; g < npwx; g += 64) emit(g, g < npw ? x[g] : cplx<T>{T(0), T(0)});
+  }
+}
+
+// The projector rows of one k in LDS, read by all its bands: one workgroup per
+// (k, group of up to kSBandsPerBlock rows).  Each row is handled by a half
+// wavefront (32 lanes, two rows per wave at a time), which halves the cost of
+// the lane reductions and of forming delta per row compared with a whole wave
+// per row; each lane keeps its NPL plane waves (g = l + 32 i) of the row in
+// registers.  Used when beta_k fits the LDS budget; it replaces the per-row
+// L2 reads of beta (nproj rows per band, twice) by LDS reads.
+constexpr int kSBandsPerBlock = 8;
+
+// sum over the 32 lanes of each half of the wavefront, on every lane
+template <class T>
+__device__ __forceinline__ T half_sum(T v) {
+  v += dpp<0xB1>(v);   // quad_perm 1,0,3,2
+  v += dpp<0x4E>(v);   // quad_perm 2,3,0,1
+  v += dpp<0x141>(v);  // row_half_mirror
+  v += dpp<0x140>(v);  // row_mirror
+  v += __shfl_xor(v, 16, 64);
+  return v;
+}
+
+template <class T, int NP, int NPL>
+__global__ __launch_bounds__(kSThreads) void spsi_lds_kernel(const cplx<T>* psi, cplx<T>* out, long kstride,
+                                                             int nvec, const int* __restrict__ off,
+                                                             const int* __restrict__ cnt,
+                                                             const int* __restrict__ live,
+                                                             const int* __restrict__ npw_k, int npwx, int nproj,
+                                                             const cplx<T>* __restrict__ beta,
+                                                             const cplx<T>* __restrict__ q,
+                                                             const double* __restrict__ scale, double mult,
+                                                             int per_xcd, int ngroup, int groups_per_k) {
+  extern __shared__ char smem[];
+  auto* qs = reinterpret_cast<cplx<T>*>(smem);        // q, nproj x nproj
+  cplx<T>* bs = qs + nproj * nproj;                   // beta_k, nproj x npw_k (row stride npwx)
+  const int bid = blockIdx.x;
+  const int grp = (bid & 7) * per_xcd + (bid >> 3);
+  if (grp >= ngroup) return;                          // whole workgroup: no barrier skipped
+  const int k = grp / groups_per_k;
+  const int r0 = (grp - k * groups_per_k) * kSBandsPerBlock;
+  const int nrow = min(kSBandsPerBlock, (cnt ? cnt[k] : nvec) - r0);
+  if (nrow <= 0) return;
+  const int npw = npw_k[k];
+  const cplx<T>* bk = beta + (long)k * nproj * npwx;
+  for (int e = threadIdx.x; e < nproj * nproj; e += kSThreads) qs[e] = q[e];
+  for (int p = 0; p < nproj; ++p)
+    for (int g = threadIdx.x; g < npw; g += kSThreads) bs[p * npwx + g] = bk[(long)p * npwx + g];
+  __syncthreads();
+  const int l = threadIdx.x & 31, half = threadIdx.x >> 5;
+  // both halves of a wave run the same number of iterations (the row index
+  // is clamped and the surplus half masked), so the lane sums see every lane
+  constexpr int NH = kSThreads / 32;
+  for (int rb = 0; rb < nrow; rb += NH) {
+    const int rr = rb + half;
+    const bool on = rr < nrow;
+    const int r = r0 + (on ? rr : 0);
+    const int task = k * nvec + r;
+    const bool act = on && !(live && !live[task]);
+    const long row = (long)k * kstride + (long)((off ? off[k] : 0) + r) * npwx;
+    const cplx<T>* x = psi + row;
+    cplx<T>* y = out + row;
+    cplx<T> xr[NPL];
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+      const int g = l + 32 * i;
+      xr[i] = (act && g < npw) ? x[g] : cplx<T>{T(0), T(0)};
+    }
+    T lr[NP], li[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) lr[p] = li[p] = T(0);
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+      const int g = l + 32 * i;
+      if (g < npw) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          if (p < nproj) {
+            const cplx<T> bv = bs[p * npwx + g];
+            lr[p] += bv.x * xr[i].x + bv.y * xr[i].y;
+            li[p] += bv.x * xr[i].y - bv.y * xr[i].x;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (p < nproj) {
+        lr[p] = half_sum(lr[p]);
+        li[p] = half_sum(li[p]);
+      }
+    }
+    T dr[NP], di[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      dr[p] = di[p] = T(0);
+      if (p < nproj) {
+#pragma unroll
+        for (int s2 = 0; s2 < NP; ++s2) {
+          if (s2 < nproj) {
+            const cplx<T> qq = qs[p * nproj + s2];
+            dr[p] += qq.x * lr[s2] - qq.y * li[s2];
+            di[p] += qq.x * li[s2] + qq.y * lr[s2];
+          }
+        }
+      }
+    }
+    if (!act) continue;
+    const T f = scale ? T(mult * scale[task]) : T(1);
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) {
+      const int g = l + 32 * i;
+      if (g >= npwx) continue;
+      if (g >= npw) {
+        if (!scale) y[g] = {T(0), T(0)};
+        continue;
+      }
+      cplx<T> v = xr[i];
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        if (p < nproj) {
+          const cplx<T> bv = bs[p * npwx + g];
+          v.x += dr[p] * bv.x - di[p] * bv.y;
+          v.y += dr[p] * bv.y + di[p] * bv.x;
+        }
+      }
+      if (scale) {
+        const cplx<T> o = y[g];
+        y[g] = {o.x + f * v.x, o.y + f * v.y};
+      } else {
+        y[g] = v;
+      }
+    }
+  }
 }
 
 template <class T, int TW, bool P16>
@@ -351,37 +506,90 @@ void launch_spsi_tw(pw_ctx* c, const VecSel& sel, const void* psi, void* out, co
 #undef MKPW_SPSI
 }
 
-template <class T, int NP>
-void launch_spsi_any(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
-                     int nproj, const void* beta, const void* q, hipStream_t st) {
+constexpr size_t kSLdsBudget = 64 * 1024;
+
+template <class T, int NP, int NPL>
+void launch_spsi_lanes_t(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
+                   int nproj, const void* beta, const void* q, hipStream_t st) {
+  if constexpr (NPL > 0) {
+    const size_t lds_b = sizeof(cplx<T>) * ((size_t)nproj * nproj + (size_t)nproj * c->npwx);
+    if (nproj > 0 && lds_b <= kSLdsBudget) {
+      const int groups_per_k = (sel.nvec + kSBandsPerBlock - 1) / kSBandsPerBlock;
+      const int ngroup = groups_per_k * c->nk;
+      const int per_xcd = (ngroup + 7) / 8;
+      hipLaunchKernelGGL((spsi_lds_kernel<T, NP, 2 * NPL>), dim3(8u * (unsigned)per_xcd), dim3(kSThreads), lds_b,
+                         st, (const cplx<T>*)psi, (cplx<T>*)out, sel.kstride, sel.nvec, sel.off, sel.cnt, sel.live,
+                         c->d_npw, c->npwx, nproj, (const cplx<T>*)beta, (const cplx<T>*)q, scale, mult, per_xcd,
+                         ngroup, groups_per_k);
+      return;
+    }
+  }
   const int ntask = sel.nvec * c->nk;
   const int nblk = (ntask + kSThreads / 64 - 1) / (kSThreads / 64);
   const int per_xcd = (nblk + 7) / 8;
   const size_t lds = sizeof(cplx<T>) * (size_t)std::max(1, nproj * nproj);
-  hipLaunchKernelGGL((spsi_kernel<T, NP>), dim3(8u * (unsigned)per_xcd), dim3(kSThreads), lds, st,
+  hipLaunchKernelGGL((spsi_kernel<T, NP, NPL>), dim3(8u * (unsigned)per_xcd), dim3(kSThreads), lds, st,
                      (const cplx<T>*)psi, (cplx<T>*)out, sel.kstride, sel.nvec, sel.off, sel.cnt, sel.live, c->d_npw,
                      c->npwx, nproj, (const cplx<T>*)beta, (const cplx<T>*)q, scale, mult, per_xcd, ntask);
+}
+
+template <class T, int NP>
+void launch_spsi_lanes(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
+                     int nproj, const void* beta, const void* q, hipStream_t st) {
+  const int chunks = (c->npwx + 63) / 64;
+  if (chunks <= 2)
+    launch_spsi_lanes_t<T, NP, 2>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else if (chunks <= 4)
+    launch_spsi_lanes_t<T, NP, 4>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else if (chunks <= 6)
+    launch_spsi_lanes_t<T, NP, 6>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else if (chunks <= 8)
+    launch_spsi_lanes_t<T, NP, 8>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else if (chunks <= 12)
+    launch_spsi_lanes_t<T, NP, 12>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else if (chunks <= 16)
+    launch_spsi_lanes_t<T, NP, 16>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  else
+    launch_spsi_lanes_t<T, NP, 0>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+}
+
+// Whether the matrix-core kernel takes less time than the others, which it does where
+// the projectors are enough to fill its products: its time does not depend on them up
+// to 8, theirs grows with them; it takes rows in groups of eight and holds them in
+// tiles of 64 x {1 .. 8, 12, 16} plane waves.  By size (us, vector units / it):
+//   * over 8 projectors: 1500 k x 8 rows [320], 9 projectors, FP64 359 / 71; not for
+//     single complex64 rows that are long: 1500 k x 1 [832] 9 projectors 90 / 118;
+//   * launches of up to 256 groups, where the latency of a group counts, from 4: 60 k x
+//     20 [320] FP64 4 projectors 15 / 12, 8 22 / 12;
+//   * FP64: [64 .. 256] from 5 (1500 k x 20 [256] 5 79 / 74, 4 70 / 67 but 4 63 / 69 at
+//     128), [320] from 3 (4 122 / 93), [448] from 5 (4 151 / 152), [576, 640] from 8 (6
+//     282 / 305), longer rows, whose projectors pass the LDS budget of the others, from 3;
+//   * complex64: its products are no faster than half waves: 1500 k x 20 [320], 8
+//     projectors 78 / 80, 4 48 / 67; rows of over 832 from 7.
+// Groups of fewer than four rows fill their tiles in vain where rows are long: 1500 k x
+// 1 [832], FP64, 8 projectors 82 / 109.
+inline bool spsi_on_matrix_cores(int real, int nk, int nvec, int npwx, int nproj) {
+  if (nproj > kSMfmaProj || npwx > kSMfmaRow) return false;
+  if (nproj > 8) return real == 8 || nvec > 1 || npwx <= 512 || nproj > 12 || nk <= 512;
+  if ((long)nk * ((nvec + kSBands - 1) / kSBands) <= 256) return nproj >= 4;
+  if (npwx > 512 && nvec < 4) return false;
+  if (real != 8) return npwx > 832 && nproj >= 7;
+  return nproj >= (npwx <= 256 ? 5 : npwx <= 320 ? 3 : npwx <= 512 ? 5 : npwx <= 640 ? 8 : 3);
 }
 
 template <class T>
 void launch_spsi_t(pw_ctx* c, const VecSel& sel, const void* psi, void* out, const double* scale, double mult,
                    int nproj, const void* beta, const void* q, hipStream_t st) {
-  // the matrix-core kernel holds lambda in one tile of rows and a row of psi in
-  // the registers of four waves
-  if (nproj <= kSMfmaProj && c->npwx <= kSMfmaRow) {
+  if (spsi_on_matrix_cores(sizeof(T), c->nk, sel.nvec, c->npwx, nproj)) {
     if (nproj <= 8)
       launch_spsi_tw<T, false>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
     else
       launch_spsi_tw<T, true>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
-    return;
+  } else if (nproj <= 8) {  // rows held in registers
+    launch_spsi_lanes<T, 8>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
+  } else {  // one wave per row looping over the plane waves
+    launch_spsi_lanes_t<T, kSMaxProj, 0>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
   }
-  // longer rows and more projectors: lambda and delta of 32 take the registers that
-  // five waves have with those of 8 (200 k x 20 rows [1088], FP64, 8 projectors: 103
-  // us against 325 with the kernel of 32)
-  if (nproj <= 8)
-    launch_spsi_any<T, 8>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
-  else
-    launch_spsi_any<T, kSMaxProj>(c, sel, psi, out, scale, mult, nproj, beta, q, st);
 }
 
 }  // namespace

@@ -8,6 +8,6 @@ from test_gpu_spsi_tiles import test_tile_edges as _edges
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nbnd,nproj", [(5, 1), (6, 8), (2, 9), (1, 16)])
+@pytest.mark.parametrize("nbnd,nproj", [(6, 8), (2, 9)])
 def test_long_rows(nbnd, nproj):
     _edges(70.0, nbnd, nproj)
