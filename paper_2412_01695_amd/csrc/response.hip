@@ -289,8 +289,8 @@ __global__ __launch_bounds__(kDvWaves * 64) void dvpsi_mfma_kernel(
 }
 
 // The same product where the box fits in LDS: one workgroup of eight waves per
-// CU stages the box once and takes its (k, band group, run of row tiles) units
-// in turn, each wave up to dvl_tiles(NG) tiles that share the B values.  psi is
+// CU stages the box once and takes its (k, eight bands, run of row tiles) units
+// in turn, each wave up to kDlTiles tiles that share the B values.  psi is
 // staged in Miller order through the permutation (one value per work-item, the
 // next block's on its way under this block's products); blocks past the sphere
 // hold zeros, and the column offsets there repeat the last one's.  The tables of
@@ -299,29 +299,30 @@ __global__ __launch_bounds__(kDvWaves * 64) void dvpsi_mfma_kernel(
 // for a pass that put psi in Miller order.  The matrix cores are busy 58% of
 // the time at the clock they run at under this load; blocks twice as long and
 // reads issued two steps ahead changed nothing, tiles in turn instead of
-// interleaved took 315 us.
+// interleaved took 315 us.  Units of sixteen bands, which read each entry for twice
+// as many, leave a wave two tiles and were slower at every band count (the whole call,
+// 1000 k: 16 bands 522 us against 458 in eights, 17 876 against 621, 33 1355 against
+// 1076).
 constexpr int kDlWaves = 8;
-__host__ __device__ constexpr int dvl_tiles(int ng) { return ng == 1 ? 3 : 2; }  // of a wave, what its registers hold
-__host__ __device__ constexpr int dvl_steps(int ng) { return ng == 1 ? 4 : 2; }  // of four plane waves, issued together
-__host__ __device__ constexpr size_t dvl_lds_bytes(long nbox, int ng, int kc, int npwx_in) {
-  return sizeof(cd) * ((size_t)nbox + 2 * (size_t)(8 * ng) * (kc + 1)) + 4 * sizeof(int) * (size_t)npwx_in;
+constexpr int kDlTiles = 3;  // of a wave, what its registers hold
+constexpr int kDlSteps = 4;  // of four plane waves, issued together
+__host__ __device__ constexpr size_t dvl_lds_bytes(long nbox, int kc, int npwx_in) {
+  return sizeof(cd) * ((size_t)nbox + 2 * 8 * (size_t)(kc + 1)) + 4 * sizeof(int) * (size_t)npwx_in;
 }
 
-template <int NG, int NT>
-__device__ __forceinline__ void dvl_block(const char* bx, const int* wc, int nch, const int (&prow)[dvl_tiles(NG)],
-                                          const double* const (&bl)[NG], int kq, mf64x4 (&d1)[dvl_tiles(NG)][NG],
-                                          mf64x4 (&d2)[dvl_tiles(NG)][NG]) {
+template <int NT>
+__device__ __forceinline__ void dvl_block(const char* bx, const int* wc, int nch, const int (&prow)[kDlTiles],
+                                          const double* bl, int kq, mf64x4 (&d1)[kDlTiles], mf64x4 (&d2)[kDlTiles]) {
   typedef double lds2 __attribute__((ext_vector_type(2)));
-  constexpr int kU = dvl_steps(NG);
+  constexpr int kU = kDlSteps;
   for (int c = 0; c < nch; ++c) {
-    double bv[kU][NG];
+    double bv[kU];
     lds2 av[kU][NT];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       const int g = 4 * (c * kU + u) + kq;
       const int w = wc[g];
-#pragma unroll
-      for (int j = 0; j < NG; ++j) bv[u][j] = bl[j][2 * g];
+      bv[u] = bl[2 * g];
 #pragma unroll
       for (int i = 0; i < NT; ++i) av[u][i] = *reinterpret_cast<const lds2*>(bx + (prow[i] + w));
     }
@@ -329,24 +330,20 @@ __device__ __forceinline__ void dvl_block(const char* bx, const int* wc, int nch
     for (int u = 0; u < kU; ++u) {
 #pragma unroll
       for (int i = 0; i < NT; ++i) {
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-          d1[i][j] = mfma_16x16x4(av[u][i][0], bv[u][j], d1[i][j]);
-          d2[i][j] = mfma_16x16x4(av[u][i][1], bv[u][j], d2[i][j]);
-        }
+        d1[i] = mfma_16x16x4(av[u][i][0], bv[u], d1[i]);
+        d2[i] = mfma_16x16x4(av[u][i][1], bv[u], d2[i]);
       }
     }
   }
 }
 
-template <int NG>
 __global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
     const cd* __restrict__ box, int nbox, int s2, int s3, int lo1, int lo2, int lo3, int kcs,
     const int* __restrict__ npw_in, const int* __restrict__ key_in, const int* __restrict__ perm_in, int npwx_in,
     const cd* __restrict__ psi, const int* __restrict__ npw_out, const int* __restrict__ key_out,
     const int* __restrict__ perm_out, int npwx_out, cd* __restrict__ out, int nk, int nbnd, int nsplit,
     double scale) {
-  constexpr int NB = 8 * NG, kDlTiles = dvl_tiles(NG);
+  constexpr int NB = 8;
   extern __shared__ __align__(16) char smem[];
   const int KC = 1 << kcs, BS = KC + 1;
   cd* Bs = reinterpret_cast<cd*>(smem) + nbox;           // [2][NB][BS]
@@ -405,11 +402,9 @@ __global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
   for (;;) {
     const bool more = un + (int)gridDim.x < nunit;
     Unit nv;
-    mf64x4 d1[kDlTiles][NG], d2[kDlTiles][NG];
+    mf64x4 d1[kDlTiles], d2[kDlTiles];
 #pragma unroll
-    for (int i = 0; i < kDlTiles; ++i)
-#pragma unroll
-      for (int j = 0; j < NG; ++j) d1[i][j] = d2[i][j] = mf64x4{0.0, 0.0, 0.0, 0.0};
+    for (int i = 0; i < kDlTiles; ++i) d1[i] = d2[i] = mf64x4{0.0, 0.0, 0.0, 0.0};
     const int* wc = wcol + which * npwx_in;
     for (int b0 = 0; b0 < v.nin; b0 += KC, buf ^= 1) {
       cd* bb = Bs + buf * NB * BS;
@@ -420,13 +415,11 @@ __global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
         nv = unit(un + gridDim.x);
         tables(nv, which ^ 1);
       }
-      const double* bl[NG];
-#pragma unroll
-      for (int j = 0; j < NG; ++j) bl[j] = reinterpret_cast<const double*>(bb + (j * 8 + (l16 & 7)) * BS) + part;
-      const int nch = (min(KC, v.nin - b0) + 4 * dvl_steps(NG) - 1) / (4 * dvl_steps(NG));
-      if (v.nt == kDlTiles) dvl_block<NG, kDlTiles>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
-      else if (kDlTiles > 2 && v.nt == 2) dvl_block<NG, 2>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
-      else if (v.nt == 1) dvl_block<NG, 1>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+      const double* bl = reinterpret_cast<const double*>(bb + (l16 & 7) * BS) + part;
+      const int nch = (min(KC, v.nin - b0) + 4 * kDlSteps - 1) / (4 * kDlSteps);
+      if (v.nt == 3) dvl_block<3>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+      else if (v.nt == 2) dvl_block<2>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
+      else if (v.nt == 1) dvl_block<1>(smem, wc + b0, nch, v.prow, bl, kq, d1, d2);
     }
     if (more) {
       if (v.nin <= 0) {
@@ -439,20 +432,16 @@ __global__ __launch_bounds__(kDlWaves * 64) void dvpsi_lds_kernel(
     // lane (kq, c), c < 8: D1 and D2 of band column c, its partner lane c + 8
     // those of the imaginary column: Re = D1[c] - D2[c + 8], Im = D1[c + 8] + D2[c]
     const int* pk = perm_out + (long)v.k * npwx_out;
+    const int ob = v.bt * NB + (l16 & 7);
+    cd* orow = out + ((long)v.k * nbnd + (ob < nbnd ? ob : 0)) * npwx_out;
 #pragma unroll
     for (int i = 0; i < kDlTiles; ++i) {
       if (i >= v.nt) break;
 #pragma unroll
-      for (int j = 0; j < NG; ++j) {
-        const int ob = v.bt * NB + j * 8 + (l16 & 7);
-        cd* orow = out + ((long)v.k * nbnd + (ob < nbnd ? ob : 0)) * npwx_out;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const double o1 = __shfl_xor(d1[i][j][r], 8, 64), o2 = __shfl_xor(d2[i][j][r], 8, 64);
-          const int gq = (v.t0 + wave + kDlWaves * i) * 16 + 4 * r + kq;
-          if (part == 0 && ob < nbnd && gq < v.nout)
-            orow[pk[gq]] = {scale * (d1[i][j][r] - o2), scale * (o1 + d2[i][j][r])};
-        }
+      for (int r = 0; r < 4; ++r) {
+        const double o1 = __shfl_xor(d1[i][r], 8, 64), o2 = __shfl_xor(d2[i][r], 8, 64);
+        const int gq = (v.t0 + wave + kDlWaves * i) * 16 + 4 * r + kq;
+        if (part == 0 && ob < nbnd && gq < v.nout) orow[pk[gq]] = {scale * (d1[i][r] - o2), scale * (o1 + d2[i][r])};
       }
     }
     // the padding of the k+q rows
@@ -790,29 +779,22 @@ extern "C" pw_status pw_dfpt_rhs(pw_ctx* ckq, const pw_ctx* ck, int nocc, const 
   hipLaunchKernelGGL(dv_box_kernel, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st, dvt, ckq->fft[0],
                      ckq->fft[1], ckq->fft[2], lo[0], lo[1], lo[2], sz[0], sz[1], sz[2], box);
   // in LDS where it fits beside a block of psi
-  const int gl = nocc <= 8 ? 1 : 2;
   const size_t room = 160 * 1024;
-  int kcs = gl == 1 ? 6 : 5;  // 64 / gl plane waves a block, or half as many
-  const bool in_lds = nbox <= (long)(room / sizeof(cd)) &&
-                      (dvl_lds_bytes(nbox, gl, 1 << kcs, ck->npwx) <= room ||
-                       dvl_lds_bytes(nbox, gl, 1 << --kcs, ck->npwx) <= room);
+  int kcs = 6;  // 64 plane waves a block, or half as many
+  const bool in_lds = nbox <= (long)(room / sizeof(cd)) && (dvl_lds_bytes(nbox, 1 << kcs, ck->npwx) <= room ||
+                                                            dvl_lds_bytes(nbox, 1 << --kcs, ck->npwx) <= room);
   if (in_lds) {
-    const int tiles = (ckq->npwmax + 15) / 16, nbt = (nocc + 8 * gl - 1) / (8 * gl);
+    const int tiles = (ckq->npwmax + 15) / 16, nbt = (nocc + 7) / 8;
     // few k: as many runs of row tiles as give every CU a workgroup, at least
     // a tile per wave
-    const int most = (tiles + kDlWaves - 1) / kDlWaves, least = (tiles + kDlWaves * dvl_tiles(gl) - 1) / (kDlWaves * dvl_tiles(gl));
+    const int most = (tiles + kDlWaves - 1) / kDlWaves, least = (tiles + kDlWaves * kDlTiles - 1) / (kDlWaves * kDlTiles);
     const int nsplit = std::max(std::max(1, least), std::min(most, 256 / std::max(1, nk * nbt)));
-    const size_t lds = dvl_lds_bytes(nbox, gl, 1 << kcs, ck->npwx);
-    const void* kern = gl == 1 ? (const void*)dvpsi_lds_kernel<1> : (const void*)dvpsi_lds_kernel<2>;
-    MKPW_TRY(ensure_lds_limit(ckq, kern, lds));
+    const size_t lds = dvl_lds_bytes(nbox, 1 << kcs, ck->npwx);
+    MKPW_TRY(ensure_lds_limit(ckq, (const void*)dvpsi_lds_kernel, lds));
     const unsigned wgs = (unsigned)std::min<long>((long)nk * nbt * nsplit, 256);
-#define MKPW_DVL(NG)                                                                                                 \
-  hipLaunchKernelGGL(dvpsi_lds_kernel<NG>, dim3(wgs), dim3(kDlWaves * 64), lds, st, box, (int)nbox, sz[1], sz[2], lo[0], \
-                     lo[1], lo[2], kcs, ck->d_npw, ck->d_mkey, ck->d_lexperm, ck->npwx, (const cd*)psi_k, ckq->d_npw, \
-                     ckq->d_mkey, ckq->d_lexperm, ckq->npwx, (cd*)rhs, nk, nocc, nsplit, -1.0)
-    if (gl == 1) MKPW_DVL(1);
-    else MKPW_DVL(2);
-#undef MKPW_DVL
+    hipLaunchKernelGGL(dvpsi_lds_kernel, dim3(wgs), dim3(kDlWaves * 64), lds, st, box, (int)nbox, sz[1], sz[2], lo[0],
+                       lo[1], lo[2], kcs, ck->d_npw, ck->d_mkey, ck->d_lexperm, ck->npwx, (const cd*)psi_k, ckq->d_npw,
+                       ckq->d_mkey, ckq->d_lexperm, ckq->npwx, (cd*)rhs, nk, nocc, nsplit, -1.0);
     MKPW_TRY(check_launch(ckq, "dvpsi", st));
   } else {
     // psi_k with each sphere in Miller order (with the k+q rows also taken in
