@@ -271,7 +271,8 @@ pw_status pw_dfpt_cg(pw_ctx* ctx, pw_prec prec, int nocc, const void* psi_occ, c
  * perturbing potential in Ha.  psi_k: device complex128 (nk, nocc, npwx_k),
  * the occupied states at k.  psi_occ_kq: device complex128 (nk, nocc,
  * npwx_kq), the S-orthonormal occupied states at k+q (S of ctx_kq).
- * rhs: device complex128 (nk, nocc, npwx_kq), written (padding zero); feed it
+ * rhs: device complex128 (nk, nocc, npwx_kq), written (padding zero); it may
+ * overlap psi_k (not psi_occ_kq); feed it
  * to pw_dfpt_cg on ctx_kq with psi_occ_kq and the eigenvalues at k.
  * 1 <= nocc <= 64.  FP64. */
 pw_status pw_dfpt_rhs(pw_ctx* ctx_kq, const pw_ctx* ctx_k, int nocc, const void* dv_r, const void* psi_k,

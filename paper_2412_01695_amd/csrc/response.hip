@@ -778,11 +778,16 @@ extern "C" pw_status pw_dfpt_rhs(pw_ctx* ckq, const pw_ctx* ck, int nocc, const 
   MKPW_TRY(b.get((size_t)nbox, &box));
   hipLaunchKernelGGL(dv_box_kernel, dim3((unsigned)((nbox + 255) / 256)), dim3(256), 0, st, dvt, ckq->fft[0],
                      ckq->fft[1], ckq->fft[2], lo[0], lo[1], lo[2], sz[0], sz[1], sz[2], box);
-  // in LDS where it fits beside a block of psi
+  // in LDS where it fits beside a block of psi, which is then read while rhs is
+  // written: where the two arrays overlap, a copy of psi is made first
+  const char *in0 = (const char*)psi_k, *out0 = (const char*)rhs;
+  const size_t in_bytes = sizeof(cd) * nk * nocc * ck->npwx, out_bytes = sizeof(cd) * nk * nocc * ckq->npwx;
+  const bool apart = in0 + in_bytes <= out0 || out0 + out_bytes <= in0;
   const size_t room = 160 * 1024;
   int kcs = 6;  // 64 plane waves a block, or half as many
-  const bool in_lds = nbox <= (long)(room / sizeof(cd)) && (dvl_lds_bytes(nbox, 1 << kcs, ck->npwx) <= room ||
-                                                            dvl_lds_bytes(nbox, 1 << --kcs, ck->npwx) <= room);
+  const bool in_lds = apart && nbox <= (long)(room / sizeof(cd)) &&
+                      (dvl_lds_bytes(nbox, 1 << kcs, ck->npwx) <= room ||
+                       dvl_lds_bytes(nbox, 1 << --kcs, ck->npwx) <= room);
   if (in_lds) {
     const int tiles = (ckq->npwmax + 15) / 16, nbt = (nocc + 7) / 8;
     // few k: as many runs of row tiles as give every CU a workgroup, at least
