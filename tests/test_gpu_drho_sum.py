@@ -5,7 +5,7 @@ One k repeated, every pair product the same value c = 1 + 2^-44 - 2^-52: adding 
 to a sum of 512 or more loses 2^-44 (almost half a unit in the last place) every
 time, and to a smaller one next to nothing.  A k has at most npw < 512 pairs in a
 bin, so k by k the sums are good to rounding; one running sum over a workgroup's 32
-k-points is 5e-14 short.  Bound: one rounding for each addition that follows, 32 k
+k-points is 4e-14 short.  Bound: one rounding for each addition that follows, 32 k
 of a workgroup, 8 boxes of a chunk, 32 chunks and three axes of 20 points,
 132 x 2^-53 = 1.5e-14 of the largest value (all terms are positive)."""
 import numpy as np
