@@ -621,6 +621,7 @@ extern std::mutex g_hpsi_tune_mu;
 extern std::map<std::vector<long>, HpsiShape> g_hpsi_tuned;
 
 constexpr size_t kLdsPerCu = 160 * 1024;
+constexpr long kFewRows = 256;
 constexpr long kTuneMinRows = 4096;  // smallest launch (in (k, band) rows) that is autotuned
 
 template <class T, int N, int WC>
@@ -855,7 +856,9 @@ pw_status launch_one(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, 
     while (sh.l3c > 1 && hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) > kLdsPerCu) --sh.l3c;
     return hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) <= kLdsPerCu;
   };
-  {
+  // a row per CU or fewer: the time of one row counts, not how many a CU takes
+  const bool few = (long)t.nk * sel.nvec <= kFewRows;
+  if (!few) {
     std::lock_guard<std::mutex> lk(g_hpsi_tune_mu);
     auto it = g_hpsi_tuned.find(key);
     if (it == g_hpsi_tuned.end() && (long)t.nk * sel.nvec < kTuneMinRows) {
@@ -877,17 +880,26 @@ pw_status launch_one(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi, 
     // 30^3 and 512 from there: 18^3 FP64 560 k x 2 33 us against 38 without the
     // convolution, 30^3 119 against 156.  Without it on 20^3 and 24^3, where the
     // order is the other way round: 20^3 FP64 1000 k x 1 34 against 38, 24^3
-    // complex64 560 k x 2 36 against 42)
+    // complex64 560 k x 2 36 against 42.  For a row per CU or fewer 512 work-items
+    // and the whole mesh as one slab on 18^3 to 24^3: 30 k x 1, 24^3 FP64, 16.3 us
+    // against 21.5, with 24 projectors 26.5 against 35.7; 18^3 11.8 against 14.3)
     HpsiShape sh;
     constexpr bool conv = WC < N && N != 20 && N != 24;
-    sh.variant = conv ? 4 : (N % 2 == 0 && N >= 30) ? 2 : 1;
-    sh.threads = N >= 30 ? 512 : 256;
+    const bool whole = few && N >= 18 && N <= 24;
+    sh.variant = whole ? 1 : conv ? 4 : (N % 2 == 0 && N >= 30) ? 2 : 1;
+    sh.threads = N >= 30 || whole ? 512 : 256;
     const int lanes = sh.variant == 2 ? 2 : 1;
     if (!hpsi_kernel_ptr<T, N, WC>(sh)) sh.threads = 256;
     const int lmax = std::min(N, std::max(1, sh.threads / (lanes * N)));
-    if (N < 30) {  // a slab that fills the work-items, two workgroups per CU
+    if (whole) {
+      sh.l3c = N;  // narrowed to what fits below
+    } else if (N < 30) {
+      // a slab that fills the work-items, two workgroups per CU; then the smallest
+      // of as many slabs (18^3 FP64, 30 k x 40: 14 planes 40 us, 9 planes 33)
       sh.l3c = lmax;
       while (sh.l3c > 1 && hpsi_lds<T, N, WC>(t, sh.l3c, nproj, sh.threads) > kLdsPerCu / 2) --sh.l3c;
+      const int slabs = (N + sh.l3c - 1) / sh.l3c;
+      sh.l3c = (N + slabs - 1) / slabs;
     } else {
       // each pass over a slab takes about one line's latency: the fewest passes
       // per row and workgroup that a CU holds, the smaller slab of equals (two
