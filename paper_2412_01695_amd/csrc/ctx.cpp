@@ -186,7 +186,7 @@ void free_kdata(pw_ctx* c) {
     dev_free(c, *p);
     *p = nullptr;
   }
-  c->kmesh = 0;
+  c->kmesh = c->kept_mesh = c->kept_half = 0;
   c->have_k = false;
   c->have_proj = false;
   c->nproj = 0;
@@ -195,13 +195,13 @@ void free_kdata(pw_ctx* c) {
 
 void free_all(pw_ctx* c) {
   free_kdata(c);
-  for (void** p : {(void**)&c->d_v64, (void**)&c->d_v32, (void**)&c->d_dij64, (void**)&c->d_dij32,
-                   (void**)&c->d_vperm64, (void**)&c->d_vperm32, (void**)&c->d_xtaps64, (void**)&c->d_xtaps32}) {
+  for (void** p : {(void**)&c->d_v64, (void**)&c->d_v32, (void**)&c->d_dij64, (void**)&c->d_dij32, &c->d_vperm64[0],
+                   &c->d_vperm64[1], &c->d_vperm32[0], &c->d_vperm32[1], &c->d_xtaps64[0], &c->d_xtaps64[1],
+                   &c->d_xtaps32[0], &c->d_xtaps32[1]}) {
     dev_free(c, *p);
     *p = nullptr;
   }
-  c->vperm_key64 = c->vperm_key32 = 0;
-  c->xtaps_key64 = c->xtaps_key32 = 0;
+  c->stale_potential();
   c->have_v = false;
 }
 
@@ -669,8 +669,7 @@ pw_status pw_set_vloc(pw_ctx* c, const double* v) {
   dev_free(c, c->d_v32);
   c->d_v64 = nullptr;
   c->d_v32 = nullptr;
-  c->vperm_key64 = c->vperm_key32 = 0;  // permuted copies and x taps are rebuilt from the new potential
-  c->xtaps_key64 = c->xtaps_key32 = 0;
+  c->stale_potential();
   c->have_v = false;
   pw_status s;
   if ((s = upload(c, v64.data(), nr, &c->d_v64)) != PW_OK) return s;

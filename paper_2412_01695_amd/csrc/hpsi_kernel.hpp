@@ -25,6 +25,7 @@
 
 #include <algorithm>
 #include <cstdio>
+#include <cstdlib>
 #include <map>
 #include <mutex>
 #include <string>
@@ -703,6 +704,7 @@ pw_status launch_shape(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi
   const bool own_mesh = N == c->fft[0];
   const double* v64 = own_mesh ? c->d_v64 : (const double*)c->d_vk64;
   const T* v = fp64 ? (const T*)(const void*)v64 : (const T*)(own_mesh ? (const void*)c->d_v32 : c->d_vk32);
+  const int set = own_mesh ? 0 : 1;
   void* vp = vscratch;
   const size_t taps_bytes = (size_t)N * N * (2 * WC - 1) * sizeof(cplx<T>);
   if (sh.variant >= 4) {
@@ -711,13 +713,17 @@ pw_status launch_shape(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi
       hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, v64, (cplx<T>*)vscratch, N, WC);
     } else {
       const int key = N << 8 | WC;
-      int& have = fp64 ? c->xtaps_key64 : c->xtaps_key32;
-      void*& own = fp64 ? c->d_xtaps64 : c->d_xtaps32;
+      int& have = fp64 ? c->xtaps_key64[set] : c->xtaps_key32[set];
+      void*& own = fp64 ? c->d_xtaps64[set] : c->d_xtaps32[set];
       if (have != key || !own) {
-        dev_free(c, own);
-        own = nullptr;
-        pw_status s = dev_alloc(c, taps_bytes, &own);
-        if (s != PW_OK) return s;
+        if (have != -key) {
+          dev_free(c, own);
+          own = nullptr;
+        }
+        if (!own) {
+          pw_status s = dev_alloc(c, taps_bytes, &own);
+          if (s != PW_OK) return s;
+        }
         hipLaunchKernelGGL(xtaps_kernel<T>, dim3(256), dim3(256), 0, st, v64, (cplx<T>*)own, N, WC);
         have = key;
       }
@@ -728,10 +734,10 @@ pw_status launch_shape(pw_ctx* c, const VecSel& sel, const void* psi, void* hpsi
   } else {
     // permuted potential for this mesh and slab width (rebuilt when they change)
     const int key = N << 8 | l3c;
-    int& have = fp64 ? c->vperm_key64 : c->vperm_key32;
-    void*& own = fp64 ? c->d_vperm64 : c->d_vperm32;
+    int& have = fp64 ? c->vperm_key64[set] : c->vperm_key32[set];
+    void*& own = fp64 ? c->d_vperm64[set] : c->d_vperm32[set];
     if (have != key || !own) {
-      if (have >> 8 != N) {
+      if (std::abs(have) >> 8 != N) {
         dev_free(c, own);
         own = nullptr;
       }

@@ -9,8 +9,11 @@
 // with a window of 11 that is 24^3, 3.4 times fewer points (1728 k x 24 bands:
 // 4.11 -> 1.86 ms in FP64, 1.82 -> 0.90 ms in complex64), for 30^3 and 24^3 with
 // a window of 10 it is 20^3 (2048 k x 16 bands at 30^3 in complex64: 0.87 -> 0.46
-// ms; 512 k x 20 bands at 24^3 in FP64: 0.38 -> 0.32 ms).  There is no choice to
-// make by size: fewer points are less work in every pass.
+// ms; 512 k x 20 bands at 24^3 in FP64: 0.38 -> 0.32 ms).  Fewer points are less
+// work in every pass: over meshes of 15^3 to 36^3, 4 to 32 projectors and both
+// precisions launches of 300 to 1000 k took 0.30 to 1.02 times as long as on the
+// context's mesh with shapes tuned for them (launches of few rows need shapes of their
+// own, launch_one in hpsi_kernel.hpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -115,17 +118,17 @@ void hpsi_potential_build(pw_ctx* c) {
       dev_free(c, *p);
       *p = nullptr;
     }
+    c->kmesh = c->kept_mesh = c->kept_half = 0;
   };
-  drop();
-  c->kmesh = 0;
-  c->vperm_key64 = c->vperm_key32 = 0;  // copies made for the kernels are rebuilt
-  c->xtaps_key64 = c->xtaps_key32 = 0;
+  c->stale_potential();
   const int n = c->fft[0];
-  if (!hpsi_supported(c->fft[0], c->fft[1], c->fft[2])) return;
+  if (!hpsi_supported(c->fft[0], c->fft[1], c->fft[2])) return drop();
   const int w[3] = {c->wx, c->wy, c->wz};
   int m = hpsi_mesh_at_least(2 * std::max(w[0], std::max(w[1], w[2])) - 1);
   if (m >= n) m = 0;
   const long half = hpsi_dense_box(c);
+  // (a new V on the same k-list is put in the same arrays)
+  if (m != c->kept_mesh || half != c->kept_half) drop();
   if (m == 0 && half == 0) return;
   const long d1 = 2 * w[0] - 1, d2 = 2 * w[1] - 1, d3 = 2 * w[2] - 1, nr = (long)m * m * m;
   // two work arrays for the passes; without memory for them or for what is kept
@@ -133,7 +136,7 @@ void hpsi_potential_build(pw_ctx* c) {
   const std::string err = c->err;
   const long most = std::max({d1 * n * n, d1 * d2 * n, d1 * d2 * d3, nr});
   void *a = nullptr, *b = nullptr;
-  auto get = [&](long bytes, void** p) { return dev_alloc(c, (size_t)bytes, p, true) == PW_OK; };
+  auto get = [&](long bytes, void** p) { return *p || dev_alloc(c, (size_t)bytes, p, true) == PW_OK; };
   bool ok = get(sizeof(cd) * most, &a) && get(sizeof(cd) * most, &b) && get(sizeof(double) * nr, &c->d_vk64) &&
             get(sizeof(float) * nr, &c->d_vk32) && get(sizeof(cd) * half, &c->d_box64) &&
             get(sizeof(cplx<float>) * half, &c->d_box32);
@@ -159,7 +162,8 @@ void hpsi_potential_build(pw_ctx* c) {
   dev_free(c, a);
   dev_free(c, b);
   if (ok) {
-    c->kmesh = m;
+    c->kmesh = c->kept_mesh = m;
+    c->kept_half = (int)half;
   } else {
     drop();
     c->err = err;

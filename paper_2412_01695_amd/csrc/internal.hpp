@@ -135,12 +135,15 @@ struct pw_ctx {
   double v0 = 0.0;          // mean of V(r): its G = 0 Fourier coefficient (Ha)
   double* d_v64 = nullptr;  // V(r) / N_r
   float* d_v32 = nullptr;
-  void* d_vperm64 = nullptr;  // V/N_r permuted for the kernel's slab width
-  void* d_vperm32 = nullptr;
-  int vperm_key64 = 0, vperm_key32 = 0;  // mesh and slab width they are laid out for
-  void* d_xtaps64 = nullptr;  // x-line convolution taps of V/N_r for a window capacity
-  void* d_xtaps32 = nullptr;
-  int xtaps_key64 = 0, xtaps_key32 = 0;  // mesh and window capacity
+  // what the transforms read of V/N_r besides, [0] on the context's mesh and [1] on
+  // kmesh (apart, so that a launch on one leaves the other's as it is: a caller may
+  // have recorded launches of both)
+  void* d_vperm64[2] = {};  // permuted for the kernel's slab width
+  void* d_vperm32[2] = {};
+  int vperm_key64[2] = {}, vperm_key32[2] = {};  // mesh and slab width they are laid out for
+  void* d_xtaps64[2] = {};  // x-line convolution taps for a window capacity
+  void* d_xtaps32[2] = {};
+  int xtaps_key64[2] = {}, xtaps_key32[2] = {};  // mesh and window capacity
   int nproj = 0;
   void* d_beta64 = nullptr;  // (nk, nproj, npwx) complex double
   void* d_beta32 = nullptr;  // complex float
@@ -161,8 +164,16 @@ struct pw_ctx {
   // >= 0; hpsi_dense.hip), null where it does not fit the kernels
   void* d_box64 = nullptr;  // complex double
   void* d_box32 = nullptr;  // complex float
+  int kept_mesh = 0, kept_half = 0;  // what the four arrays above were allocated for
   int npwmax = 0;           // largest npw
 
+  // the copies of V made for the transforms are filled anew at their next launch, in
+  // place where the layout is the same (a caller may have recorded launches that read
+  // them): keys of stale copies are negative
+  void stale_potential() {
+    for (int* k : {vperm_key64, vperm_key32, xtaps_key64, xtaps_key32})
+      for (int i = 0; i < 2; ++i) k[i] = k[i] > 0 ? -k[i] : k[i];
+  }
   mkpw::KTables tables() const;
 };
 
