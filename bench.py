@@ -9,9 +9,10 @@ the 1728-k-point fcc cell (ecut 40 Ry, FFT 36^3, 24 bands, 4 projectors),
 the configuration of the FP64-vs-mixed metric; value is its FP64 throughput
 in k-band H|psi> per second, and the same batch is timed in mixed precision
 (complex64, FP32 accumulation) beside it.  The dominant kernel's roofline
-fraction is computed from the algorithmic flop count of the pruned FFT
-pipeline (see `algorithmic_work`) over its average launch time measured with
-HIP events on the launch stream.  The CPU baseline is the FP64 oracle's
+fraction is computed from the flop count of the kernel that ran (the dense
+product's, see `kernel_flops`, or the pruned FFT pipeline's, see
+`algorithmic_work`) over its average launch time measured with HIP events on
+the launch stream.  The CPU baseline is the FP64 oracle's
 dense route (H_k psi_k by zgemm per k, H_k built outside the timed region),
 on a process pool over the host cores.  Beside the step throughput it
 reports the H|psi> throughput of the 512- and 2048-k workloads, the Davidson
@@ -50,16 +51,16 @@ PEAK_HBM_GBS = 8000.0
 # counters read for a 1 GiB device-to-device copy (FETCH x 2.0, WRITE x 1.0),
 # keyed by workload, precision and launch shape, and valid only for the kernel
 # sources they were taken on (hash of the files below).
-KERNEL_SOURCES = ("hpsi_kernel.hpp", "fft.hpp", "hpsi_types.hpp", "wave.hpp")
+KERNEL_SOURCES = ("hpsi_dense.hip", "hpsi_dense_shape.hpp", "hpsi_types.hpp", "internal.hpp")
 MEASURED_TRAFFIC = {
-    ("fcc1-ecut40-fft36-1728k", "fp64", (4, 512, 14)): {
-        "sources": "f7c8de6240b6b685", "fetch_kib": 185567.0, "write_kib": 331776.0,
+    ("fcc1-ecut40-fft36-1728k", "fp64", (6, 512, 0)): {
+        "sources": "af43c389e8f90ac5", "fetch_kib": 347102.7, "write_kib": 331776.0,
         "fetch_scale": 2.0, "write_scale": 1.0,
-        "profile": "profiles/hpsi_fp64_fcc1-ecut40-fft36-1728k.md"},
-    ("fcc1-ecut40-fft36-1728k", "mixed", (5, 512, 8)): {
-        "sources": "f7c8de6240b6b685", "fetch_kib": 96364.5, "write_kib": 165888.0,
+        "profile": "profiles/hpsi_dense_fp64_fcc1-ecut40-fft36-1728k.md"},
+    ("fcc1-ecut40-fft36-1728k", "mixed", (6, 256, 0)): {
+        "sources": "af43c389e8f90ac5", "fetch_kib": 170518.0, "write_kib": 165888.0,
         "fetch_scale": 2.0, "write_scale": 1.0,
-        "profile": "profiles/hpsi_mixed_fcc1-ecut40-fft36-1728k.md"},
+        "profile": "profiles/hpsi_dense_mixed_fcc1-ecut40-fft36-1728k.md"},
 }
 
 
@@ -354,7 +355,7 @@ def overlap_sample(torch, mkpw, cfg_id, steps, warmup, solve, check):
                            f"s 16 / p 12 (two channels coupled 4 / 3)",
                "s_psi": {"ms_per_call": ms, "kband_per_s": nkb / (ms * 1e-3), "dtype": "c128",
                          "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                                      "frac": gbs / PEAK_HBM_GBS, "kernel": "spsi_kernel",
+                                      "frac": gbs / PEAK_HBM_GBS, "kernel": "spsi_mfma_kernel",
                                       "bytes_per_launch": io}}}
         eigs = {}
         for name, prec, tol in (("fp64", mkpw.PW_FP64, 1e-10), ("mixed", mkpw.PW_MIXED, 1e-6)):

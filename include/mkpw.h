@@ -113,8 +113,9 @@ pw_status pw_set_option(pw_ctx* ctx, const char* key, int64_t value);
 
 /* Read an option (the keys above), or "hpsi_variant_tuned" / "hpsi_slab_tuned" /
  * "hpsi_threads_tuned" (the shape of this context's last H|psi> launch, 0 if
- * none; variant 6 is the local term as a dense product on the matrix cores,
- * which launches without an explicit shape take where it is the faster one), "device_bytes" (device memory the context holds now), "overlap"
+ * none; variant 6, a reading and not a value of "hpsi_variant", is the local
+ * term as a dense product on the matrix cores, which launches without an
+ * explicit shape take where it is the faster one), "device_bytes" (device memory the context holds now), "overlap"
  * (1 while overlap coefficients q are set, else 0), or the context's sizes:
  * "nk" and "npwx" (0 before pw_set_kpoints), "nproj" (0 without projectors),
  * "fft1", "fft2", "fft3" (the mesh; 0 before pw_set_cutoff), and what the

@@ -9,7 +9,7 @@
 // of the Miller window occur, so the matrix is never formed: its entries are read
 // from a box of V~ values in LDS (one half of it, V being real: 74 KB in FP64 at a
 // window of 11).  8 npw^2 flop per row are no more than the transforms' at npw of a
-// few hundred, and they run on the matrix cores, where the transforms keep the
+// few hundred (dense_faster says where the line lies), and they run on the matrix cores, where the transforms keep the
 // vector units 40% (FP64) to 93% (complex64) busy.
 //
 // What bounds it: the matrix cores' issue.  Every vector instruction costs them 2
@@ -17,12 +17,14 @@
 // v_mfma_f32_16x16x4, 32), so an entry takes three (address, sign, negation) and
 // serves up to 24 vectors, and psi is staged in the form the products read.  On
 // MI355X, us (transforms on the context's mesh / on the smallest mesh / this):
-//   512 k x 20 vectors, npw 305, FP64       379 /  316 /  166  matrix cores 75% busy
-//   1728 k x 24 vectors, npw 469, FP64     4109 / 1860 / 1415  75%
-//   2048 k x 16 vectors, npw 305, complex64 870 /  461 /  258  73%
-//   1728 k x 24 vectors, npw 469, complex64 1820 / 902 /  748  75%
-// (the rest: uneven row tiles, 6%; vector instructions, 7%; the start, the
-// projectors and the output of a workgroup, 7 to 12%).  Rounding is below the
+//   512 k x 20 vectors, npw 305, FP64       379 /  316 /  163  matrix cores 66% busy
+//   1728 k x 24 vectors, npw 469, FP64     4109 / 1860 / 1420  71%
+//   2048 k x 16 vectors, npw 305, complex64 870 /  461 /  258  69%
+//   1728 k x 24 vectors, npw 469, complex64 1820 / 902 /  714  70%
+// (busy: of the cycles of the whole launch, its start and end among them; the rest:
+// uneven row tiles, vector instructions, the start, the projectors and the output of a
+// workgroup).  psi is read twice, for the product and for the kinetic term: 1.05 GB of
+// HBM traffic at 1728 k in FP64, 0.74 TB/s.  Rounding is below the
 // transforms' (complex64 3.6e-8 of the result against 5.6e-8 to 8.4e-8).  Tried
 // and dropped: entries gathered from L2 (1640 us at 1728 k, FP64: the vector
 // memory path takes 57 to 90 cycles a gather), rows in Miller order with the

@@ -59,9 +59,11 @@ constexpr int kSMfmaRow = 1024;  // longest rows
 // lambdas meet in LDS, where delta is formed.
 // Up to eight projectors the A rows of lambda hold Re beta, then Im beta (one
 // product a step); P16 takes two.
-// HBM-bound: psi read once, beta from the XCD's L2, the result written once
-// (512 k x 20 rows [305], 8 projectors, FP64: 40 us, 3.0 TB/s; half a wave per
-// row with lane sums took 68 us).
+// Bound by memory and the chain of a workgroup (load, lambda, barrier, delta, store):
+// psi is read once, beta from the XCD's L2, the result written once.  512 k x 20 rows
+// [305], 8 projectors, FP64, 120 MB, half a wave per row with lane sums / this: 56 / 36
+// us called again and again on the same rows, which the last-level cache then holds; 60
+// / 41 us (2.9 TB/s) on rows that come from HBM, twelve psi and results in turn.
 template <class T, int TW, bool P16>
 __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(TW <= 5 ? 4 : 1))) void spsi_mfma_kernel(
     const cplx<T>* psi, cplx<T>* out, long kstride, int nvec, const int* __restrict__ off,
